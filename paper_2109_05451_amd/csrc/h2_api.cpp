@@ -485,7 +485,7 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
   // ---- upload
   const int64_t mat_bytes = P.off_end - P.off_U;
   if (mat_bytes > 0) {
-    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&h->d_mat), mat_bytes), "hipMalloc(matrix data)");
+    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&h->d_mat), mat_bytes + kRowSlack), "hipMalloc(matrix data)");
     const int64_t host_bytes = d_dense ? P.off_D - P.off_U : mat_bytes;
     if (host_bytes > 0)
       HIP_TRY(hipMemcpy(h->d_mat, buf + P.off_U, host_bytes, hipMemcpyHostToDevice), "hipMemcpy(matrix data)");
@@ -499,7 +499,7 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
   if (ntrans > 0) {
     std::vector<TransTask> tasks;
     transpose_tasks(lay, &tasks);
-    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&h->d_trans), ntrans * sizeof(double)), "hipMalloc(trans)");
+    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&h->d_trans), ntrans * sizeof(double) + kRowSlack), "hipMalloc(trans)");
     HIP_TRY(hipMemset(h->d_trans, 0, ntrans * sizeof(double)), "hipMemset(trans)");
     if (!tasks.empty()) {
       TransTask* d_tasks = nullptr;
@@ -694,9 +694,9 @@ int prepare_f32(h2_op_s* h) {
   if (h->d_mat32 || h->n_lowrank + h->n_trans == 0) return H2_OK;
   float *m32 = nullptr, *t32 = nullptr;
   hipError_t e;
-  if ((e = hipMalloc(reinterpret_cast<void**>(&m32), sizeof(float) * std::max<int64_t>(h->n_lowrank, 1))) !=
+  if ((e = hipMalloc(reinterpret_cast<void**>(&m32), sizeof(float) * h->n_lowrank + kRowSlack)) !=
           hipSuccess ||
-      (e = hipMalloc(reinterpret_cast<void**>(&t32), sizeof(float) * std::max<int64_t>(h->n_trans, 1))) !=
+      (e = hipMalloc(reinterpret_cast<void**>(&t32), sizeof(float) * h->n_trans + kRowSlack)) !=
           hipSuccess) {
     if (m32) (void)hipFree(m32);
     return hip_fail(e, "hipMalloc(FP32 copy)");
@@ -756,7 +756,7 @@ int prepare_fl(h2_op_s* h, int prec) {
   };
   if (!h->d_fl) {
     double* d = nullptr;
-    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&d), sizeof(double) * h->n_fl), "hipMalloc(fragment-ordered copy)");
+    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&d), sizeof(double) * h->n_fl + kRowSlack), "hipMalloc(fragment-ordered copy)");
     const hipError_t e = make(d, false);
     if (e != hipSuccess) {
       (void)hipFree(d);
@@ -767,7 +767,7 @@ int prepare_fl(h2_op_s* h, int prec) {
   }
   if (prec == H2_PREC_FP32 && h->d_mat32 && !h->d_fl32) {
     float* d = nullptr;
-    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&d), sizeof(float) * h->n_fl), "hipMalloc(fragment-ordered copy)");
+    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&d), sizeof(float) * h->n_fl + kRowSlack), "hipMalloc(fragment-ordered copy)");
     const hipError_t e = make(d, true);
     if (e != hipSuccess) {
       (void)hipFree(d);
@@ -1360,10 +1360,10 @@ int h2_tune(h2_handle h, int64_t nv, int prec, void* stream) {
       const bool wave = kc == kWaveRows || kc == kWaveTiles;
       for (int64_t g : grids)
         for (int cand = 0; cand < (wave ? 8 : 2); ++cand) {
-          // wave-row forms: also without the copy, and the five-waves-per-SIMD form
+          // wave-row forms: also without the copy, and the form with more rows in flight
           const int remap = cand & 1, fl = wave && has_fl ? (cand >> 1) & 1 : 1, occ = cand >> 2 ? 5 : 0;
           if (wave && !has_fl && (cand >> 1) & 1) continue;
-          if (occ && !wave_occ5(nvp, L.max_rows, kc == kWaveTiles)) continue;
+          if (occ && !wave_alt(nvp)) continue;
           if (g != 0 && g >= L.row_count) continue;
           // the dense rows run beside the sweeps: a persistent grid would hold
           // every CU slot and starve them, so they keep one workgroup per row
@@ -1505,7 +1505,7 @@ int h2_tune_set(h2_handle h, int prec, int kc, int64_t grid, int xcd, int tree_o
     set_error("kc must be 0-12, 32 or 64");
     return H2_EINVAL;
   }
-  // 11, 12: the wave-row forms compiled for five waves per SIMD
+  // 11, 12: the wave-row forms with more rows in flight
   const int occ = kc == kWaveTiles + 1 || kc == kWaveTiles + 2 ? 5 : 0;
   if (occ) kc -= 2;
   if (prec == H2_PREC_BF16 && kc != 64) { set_error("the BF16 kernel has kc 64 only"); return H2_EINVAL; }

@@ -227,8 +227,8 @@ int batch_build(const void* const* bufs, const size_t* lens, int64_t count, h2_b
   }
 
   // device arena: matrix data, transposed bases, inverse permutations
-  HIP_TRYB(hipMalloc(reinterpret_cast<void**>(&b->d_mat), sizeof(double) * std::max<int64_t>(mat, 1)), "hipMalloc(arena)");
-  HIP_TRYB(hipMalloc(reinterpret_cast<void**>(&b->d_trans), sizeof(double) * std::max<int64_t>(trans, 1)), "hipMalloc(arena)");
+  HIP_TRYB(hipMalloc(reinterpret_cast<void**>(&b->d_mat), sizeof(double) * mat + kRowSlack), "hipMalloc(arena)");
+  HIP_TRYB(hipMalloc(reinterpret_cast<void**>(&b->d_trans), sizeof(double) * trans + kRowSlack), "hipMalloc(arena)");
   std::vector<int32_t> pinv(std::max<int64_t>(pin, 1));
   // the transposed bases are made on the device from the uploaded matrix
   // data: every operator's blocks, at its arena offsets
@@ -556,14 +556,14 @@ int h2_batch_tune(h2_batch b, const h2_batch_item* items, void* stream) {
         for (int kc : kcs)
           for (int64_t gsz : grids)
             for (int cand = 0; cand < 4; ++cand) {
-            // XCD ranges and the five-waves-per-SIMD form: wave-row kernels only
+            // XCD ranges and the form with more rows in flight: wave-row kernels only
             const int remap = cand & 1, occ = cand >> 1 ? 5 : 0;
             const bool wave = kc == kWaveRows || kc == kWaveTiles;
             if (gsz != 0 && gsz >= L.row_count) continue;
             if (wave && L.max_rows > 64) continue;
             if (kc == kWaveTiles && G.nvp != 32 && G.nvp != 64) continue;
             if ((remap || occ) && !wave) continue;
-            if (occ && !wave_occ5(G.nvp, L.max_rows, kc == kWaveTiles)) continue;
+            if (occ && !wave_alt(G.nvp)) continue;
             Launch T = L;
             T.kc = kc;
             T.grid = gsz;

@@ -27,6 +27,10 @@ constexpr int kMaxDim = 256;
 constexpr int kNbMax = 512;
 // Largest number of children of one node.
 constexpr int kMaxChildren = kNbMax;
+// Bytes allocated past the end of every matrix-data array: the wave-row
+// kernels read up to 64 rows and 16 columns past a row's matrix (and use
+// nothing of it), 64 * 17 * 8 bytes at most.
+constexpr int64_t kRowSlack = 16384;
 // Vectors per pass of the streaming path (one thread keeps them in registers).
 constexpr int kPassVectors = 4;
 // Vectors per pass of the MFMA path (four 16-wide tiles).
@@ -116,7 +120,7 @@ struct Launch {
   int64_t gridp[3] = {0, 0, 0};
   int remapp[3] = {0, 0, 0};  // XCD-aware row ranges
   int flp[3] = {1, 1, 1};     // wave-row kernels: read the fragment-ordered copy when there is one
-  int occp[3] = {0, 0, 0};    // wave-row kernels: 5 = the form compiled for five waves per SIMD
+  int occp[3] = {0, 0, 0};    // wave-row kernels: 5 = the form with more rows in flight
   float tuned_ms[3] = {0, 0, 0};  // time of the chosen setting when tuned (two runs)
   // sweep transfer launches: the level of the parent nodes (upsweep: whose
   // x^ it computes; downsweep: whose y^ it pushes down); -1 for other launches
@@ -454,20 +458,17 @@ hipError_t launch_permute_out_rm(const double* Z, const int32_t* pinv, double al
 // workgroups (0: enough for every row at once); remap: XCD-aware row ranges
 constexpr int kWaveRows = 9, kWaveTiles = 10;
 // fl: the fragment-ordered copy of the rows' matrices (rows' fl_off), read
-// instead of `data` when not null; occ 5: the form compiled for five waves
-// per SIMD where one exists (one 16-vector tile per wave, rows of at most 48
-// outputs), else the default; the results are bitwise the same
+// instead of `data` when not null; occ != 0: the form with more rows in flight
+// (two waves per row at 64 vectors, else half the columns per load group; none
+// at 48 vectors); the results are bitwise the same.  The matrix data must be
+// followed by kRowSlack readable bytes.
 template <typename T>
 hipError_t launch_wave_rows(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
                             const T* data, const double* in, double* out, int nvp, int mode, int max_rows,
                             hipStream_t s, int64_t grid, bool narrow = false, int remap = 0, const T* fl = nullptr,
                             int occ = 0);
-// True when launch_wave_rows has a five-waves-per-SIMD form for this pass
-// width, row length and kernel (one 16-vector tile per wave, at most three
-// 16-row tiles)
-inline bool wave_occ5(int nvp, int max_rows, bool narrow) {
-  return max_rows <= 48 && (nvp == 16 || (narrow && (nvp == 32 || nvp == 64)));
-}
+// True when launch_wave_rows has a second form (occ != 0) for this pass width
+inline bool wave_alt(int nvp) { return nvp != 48; }
 // dst[R.fl_off ...] = the fragment-ordered copy of every row's matrix at src[R.data_off ...]
 template <typename T>
 hipError_t launch_rows_to_fl(const RowDesc* rows, int64_t nrows, const int32_t* colend, const T* src, T* dst,

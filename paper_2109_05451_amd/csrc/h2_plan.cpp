@@ -172,7 +172,7 @@ void place_fl(RowTables& t, int64_t begin, int64_t end, int arr, FlKeys* keys, i
   for (int64_t i = begin; i < end; ++i) {
     RowDesc& R = t.rows[i];
     const int32_t ncols = R.blk_end > R.blk_begin ? t.colend[R.blk_end - 1] : 0;
-    const int64_t size = ((int64_t)R.nrows * ncols + 1) / 2 * 2;
+    const int64_t size = (int64_t)R.nrows * ((ncols + 7) / 8 * 8);  // columns padded to pairs of steps
     const auto ins = keys->emplace(2 * R.data_off + arr, FlRegion{*n_fl, R.nrows, ncols});
     if (!ins.second && (ins.first->second.nrows != R.nrows || ins.first->second.ncols != ncols)) {
       R.fl_off = *n_fl;  // the same offset with another shape: a region of its own
