@@ -288,10 +288,9 @@ int h2_ranks(h2_handle h, int64_t* krow, int64_t* kcol, int64_t cap);
  * passes of 64 vectors, 1-8 rows of at most 64 outputs; other launches use
  * 64 columns), 9 for one wave per row with no LDS staging (rows of at most
  * 64 outputs, any pass width), 10 the same with one wave per 16-vector tile
- * (passes of 32 or 64 vectors), 11 and 12 the forms of 9 and 10 that keep
- * more rows in flight (11 at 64 vectors two waves per row, else half the
- * columns per load group; at 48 vectors the form of 9); grid = workgroups (0 = one per
- * row); xcd != 0 for XCD-aware row ranges; tree_order != 0 for tree-ordered
+ * (passes of 32 or 64 vectors), 11 a second form of 9 (two waves per row at 64
+ * vectors, half the columns per load group at 16 and 32), 12 as 10;
+ * grid = workgroups (0 = one per row); xcd != 0 for XCD-aware row ranges; tree_order != 0 for tree-ordered
  * coupling and dense rows.  Results do not change (same summation order).  For
  * reproducible timing and for tests.  Errors: H2_EINVAL. */
 int h2_tune_set(h2_handle h, int prec, int kc, int64_t grid, int xcd, int tree_order);

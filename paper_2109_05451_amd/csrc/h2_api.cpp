@@ -97,6 +97,8 @@ void add_stream_rows(h2_op_s* h, const std::vector<RowSpec>& rows, const size_t*
     if ((int64_t)r.blks.size() <= kNbMax) {
       append_row(h->rt, r);
       narrow.max_rows = std::max(narrow.max_rows, r.nrows);
+      if (r.nrows > 0) narrow.min_rows = std::min(narrow.min_rows, r.nrows);
+      narrow.max_cols = std::max(narrow.max_cols, row_cols(r));
     } else {
       append_row(h->wide, r);
       wide.max_rows = std::max(wide.max_rows, r.nrows);
@@ -130,7 +132,10 @@ void add_gather_phase(h2_op_s* h, const std::vector<RowSpec>& rows, int in, int 
   L.out = out;
   L.mode = MODE_STORE;
   L.row_begin = (int64_t)h->gt.rows.size();
-  for (size_t i = first; i < rows.size(); i += step) append_gather(h->gt, rows[i]);
+  for (size_t i = first; i < rows.size(); i += step) {
+    append_gather(h->gt, rows[i]);
+    L.max_rows = std::max(L.max_rows, rows[i].nrows);
+  }
   L.row_count = (int64_t)h->gt.rows.size() - L.row_begin;
   if (L.row_count) dst.push_back(L);
 }
@@ -524,6 +529,16 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
                         &h->planN.couple_rest})
     for (const Launch& L : *v)
       if (L.kind != KIND_STREAM) h->mfma_ok = false;
+  // op 'T': its rows have no fragment-ordered copies, and its transposed rows
+  // take the multi-vector kernel up to 64 outputs
+  h->mfma_t_ok = h->mfma_ok;
+  for (auto* v : {&h->planT.up, &h->planT.couple, &h->planT.down, &h->planT.dense, &h->planT.dense2})
+    for (Launch& L : *v) {
+      for (int& f : L.flp) f = 0;
+      if (L.kind == KIND_WIDE || (L.kind == KIND_GATHER && L.max_rows > 64)) h->mfma_t_ok = false;
+    }
+  for (int& f : h->planT.out.flp) f = 0;
+  if (h->planT.out.kind != KIND_STREAM) h->mfma_t_ok = false;
   int64_t ib = 0;
   int rc;
   if ((rc = upload(perm, &h->d_perm, &ib)) || (rc = upload(pinv, &h->d_pinv, &ib)) || (rc = upload(h->rt.rows, &h->rt.d_rows, &ib)) ||
@@ -647,26 +662,39 @@ int run_launch(h2_op_s* h, const Workspace& w, const Launch& L, int nv, const Ep
   const int64_t grid_of = [&](int pi) {
     return (!L.lowrank && h->dense_grid_mv >= 0) ? h->dense_grid_mv : L.gridp[pi];
   }(lowp ? H2_PREC_FP32 : H2_PREC_FP64);
-  const int kcw = L.kcp[lowp ? H2_PREC_FP32 : H2_PREC_FP64];
-  if (nvp > 0 && (kcw == kWaveRows || kcw == kWaveTiles) && L.max_rows <= 64) {
+  int kcw = L.kcp[lowp ? H2_PREC_FP32 : H2_PREC_FP64], occ = L.occp[lowp ? H2_PREC_FP32 : H2_PREC_FP64];
+  if (nvp > 0 && kcw == kAutoForm) {
+    RowForm f = auto_form(nvp, L.row_count, L.max_rows);
+    // dense rows beside the BF16 sweeps, one vector tile, rows of up to 1024
+    // columns (2D): there the sweeps' chain is what the product waits for, and
+    // the LDS-staged kernel leaves it more of the memory (20 000 points 188
+    // against 204-219 us, 82 810 points 245 against 270; longer rows, 3D of
+    // 32 768 points, 784 against 649)
+    if (!L.lowrank && prec == H2_PREC_BF16 && nvp == 16 && L.max_cols <= 1024) f = {64, 0};
+    kcw = f.kc;
+    occ = f.occ;
+  }
+  if (nvp > 0 && L.kind == KIND_GATHER) {
+    e = launch_wave_cols(h->gt.d_rows + L.row_begin, L.row_count, h->gt.d_data, h->gt.d_mr, h->gt.d_in_off, data,
+                         bufs[L.in], out, nvp, L.max_rows, s);
+  } else if (nvp > 0 && (kcw == kWaveRows || kcw == kWaveTiles) && L.max_rows <= 64) {
     const bool narrow = kcw == kWaveTiles;
     const int rm = L.remapp[lowp ? H2_PREC_FP32 : H2_PREC_FP64];
     const bool fl = L.flp[lowp ? H2_PREC_FP32 : H2_PREC_FP64] != 0;
-    const int occ = L.occp[lowp ? H2_PREC_FP32 : H2_PREC_FP64];
     e = lowp ? launch_wave_rows<float>(h->rt.d_rows + L.row_begin, L.row_count, h->rt.d_colend, h->rt.d_in_off,
-                                       data32, bufs[L.in], out, nvp, mode, L.max_rows, s, grid_of, narrow, rm,
+                                       data32, bufs[L.in], out, nvp, mode, L.min_rows, L.max_rows, s, grid_of, narrow, rm,
                                        fl ? h->d_fl32 : nullptr, occ)
              : launch_wave_rows<double>(h->rt.d_rows + L.row_begin, L.row_count, h->rt.d_colend, h->rt.d_in_off,
-                                        data, bufs[L.in], out, nvp, mode, L.max_rows, s, grid_of, narrow, rm,
+                                        data, bufs[L.in], out, nvp, mode, L.min_rows, L.max_rows, s, grid_of, narrow, rm,
                                         fl ? h->d_fl : nullptr, occ);
   } else if (nvp > 0) {
     const int pi = lowp ? H2_PREC_FP32 : H2_PREC_FP64;
     const float* in32 = lowp && x32 && nvp == kPassVectorsMfma && L.in == BUF_XH ? w.xh32 : nullptr;
     e = lowp ? launch_rows_mfma<float>(h->rt.d_rows + L.row_begin, L.row_count, h->rt.d_colend, h->rt.d_in_off,
-                                       data32, bufs[L.in], out, nvp, mode, L.max_rows, s, L.kcp[pi], grid_of,
+                                       data32, bufs[L.in], out, nvp, mode, L.max_rows, s, kcw, grid_of,
                                        L.remapp[pi], in32)
              : launch_rows_mfma<double>(h->rt.d_rows + L.row_begin, L.row_count, h->rt.d_colend, h->rt.d_in_off,
-                                        data, bufs[L.in], out, nvp, mode, L.max_rows, s, L.kcp[pi], grid_of,
+                                        data, bufs[L.in], out, nvp, mode, L.max_rows, s, kcw, grid_of,
                                         L.remapp[pi]);
   } else if (L.kind == KIND_STREAM) {
     // the dense rows (beside the sweeps) hold two workgroup slots per CU, so
@@ -905,7 +933,7 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
     HIP_TRY(hipEventRecord(w.ev_fork, s), "hipEventRecord(fork)");
     HIP_TRY(hipStreamWaitEvent(w.side, w.ev_fork, 0), "hipStreamWaitEvent(fork)");
     STEP(mark(5, w.side));
-    for (const Launch& L : dense1) STEP(run_launch(h, w, L, nv, ep, w.side, nvp));
+    for (const Launch& L : dense1) STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));
     STEP(mark(9, w.side));
     return H2_OK;
   };
@@ -940,7 +968,7 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
     HIP_TRY(hipStreamWaitEvent(w.side, w.ev_mid, 0), "hipStreamWaitEvent(mid)");
   }
   STEP(mark(10, w.side));
-  for (const Launch& L : dense2) STEP(run_launch(h, w, L, nv, ep, w.side, nvp));
+  for (const Launch& L : dense2) STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));
   STEP(mark(6, w.side));
   HIP_TRY(hipEventRecord(w.ev_join, w.side), "hipEventRecord(join)");
   // Multi-vector path: the leaf expansion U y^ goes to its own buffer w.zx,
@@ -1104,8 +1132,9 @@ int gemv_ws(h2_op_s* h, const Workspace& w, bool trans, double alpha, const doub
     }
     if ((rc = prepare_bf16(h)) != H2_OK) return rc;
   }
-  // multi-vector products of op 'N' (and every BF16 product) go to the MFMA kernels
-  const bool mfma = !trans && h->mfma_ok && w.cap >= kPassVectorsMfma && (nv > kPassVectors || prec == H2_PREC_BF16);
+  // multi-vector products go to the MFMA kernels (op 'T' in FP64), and every BF16 product
+  const bool mfma = (trans ? h->mfma_t_ok && prec == H2_PREC_FP64 : h->mfma_ok) && w.cap >= kPassVectorsMfma &&
+                    (nv > kPassVectors || prec == H2_PREC_BF16);
   // (a workspace with fewer than kPassVectors columns takes passes of its width)
   const int64_t pass = mfma ? kPassVectorsMfma : std::min<int64_t>(kPassVectors, w.cap);
   for (int64_t v0 = 0; v0 < nv; v0 += pass) {
@@ -1363,7 +1392,7 @@ int h2_tune(h2_handle h, int64_t nv, int prec, void* stream) {
           // wave-row forms: also without the copy, and the form with more rows in flight
           const int remap = cand & 1, fl = wave && has_fl ? (cand >> 1) & 1 : 1, occ = cand >> 2 ? 5 : 0;
           if (wave && !has_fl && (cand >> 1) & 1) continue;
-          if (occ && !wave_alt(nvp)) continue;
+          if (occ && !wave_alt(nvp, kc == kWaveTiles)) continue;
           if (g != 0 && g >= L.row_count) continue;
           // the dense rows run beside the sweeps: a persistent grid would hold
           // every CU slot and starve them, so they keep one workgroup per row

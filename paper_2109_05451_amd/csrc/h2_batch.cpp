@@ -133,6 +133,7 @@ bool add_phase(h2_batch_s* b, std::vector<RowSpec>& rows, int arr, int mode, boo
   for (const RowSpec& r : rows) {
     append_row(b->rt, r);
     L.max_rows = std::max(L.max_rows, r.nrows);
+    if (r.nrows > 0) L.min_rows = std::min(L.min_rows, r.nrows);
   }
   L.row_count = (int64_t)b->rt.rows.size() - L.row_begin;
   dst.push_back(L);
@@ -308,16 +309,17 @@ int batch_build(const void* const* bufs, const size_t* lens, int64_t count, h2_b
 
 int run_blaunch(h2_batch_s* b, const Group& G, const Launch& L, hipStream_t s) {
   const double* data = L.arr == ARR_TRANS ? b->d_trans : b->d_mat;
-  if ((L.kc == kWaveRows || L.kc == kWaveTiles) && L.max_rows <= 64) {
+  const RowForm f = L.kc == kAutoForm ? auto_form(G.nvp, L.row_count, L.max_rows) : RowForm{L.kc, L.occp[0]};
+  if ((f.kc == kWaveRows || f.kc == kWaveTiles) && L.max_rows <= 64) {
     const hipError_t e = launch_wave_rows<double>(b->rt.d_rows + L.row_begin, L.row_count, b->rt.d_colend,
                                                   b->rt.d_in_off, data, G.d_ws, G.d_ws, G.nvp, L.mode,
-                                                  L.max_rows, s, L.grid, L.kc == kWaveTiles, L.remapp[0], nullptr,
-                                                  L.occp[0]);
+                                                  L.min_rows, L.max_rows, s, L.grid, f.kc == kWaveTiles, L.remapp[0], nullptr,
+                                                  f.occ);
     if (e != hipSuccess) return hip_fail_b(e, "batch kernel launch");
     return H2_OK;
   }
   hipError_t e = launch_rows_mfma<double>(b->rt.d_rows + L.row_begin, L.row_count, b->rt.d_colend, b->rt.d_in_off,
-                                          data, G.d_ws, G.d_ws, G.nvp, L.mode, L.max_rows, s, L.kc, L.grid);
+                                          data, G.d_ws, G.d_ws, G.nvp, L.mode, L.max_rows, s, f.kc, L.grid);
   if (e != hipSuccess) return hip_fail_b(e, "batch kernel launch");
   return H2_OK;
 }
@@ -563,7 +565,7 @@ int h2_batch_tune(h2_batch b, const h2_batch_item* items, void* stream) {
             if (wave && L.max_rows > 64) continue;
             if (kc == kWaveTiles && G.nvp != 32 && G.nvp != 64) continue;
             if ((remap || occ) && !wave) continue;
-            if (occ && !wave_alt(G.nvp)) continue;
+            if (occ && !wave_alt(G.nvp, kc == kWaveTiles)) continue;
             Launch T = L;
             T.kc = kc;
             T.grid = gsz;

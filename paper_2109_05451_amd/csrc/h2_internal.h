@@ -22,6 +22,9 @@ namespace h2 {
 // Largest rank and leaf size the kernels accept (one output entry per
 // thread of a 256-thread workgroup along the row dimension).
 constexpr int kMaxDim = 256;
+// Kernel form of a multi-vector launch that no tuner or caller set: chosen by
+// auto_form at launch, when the pass width is known.
+constexpr int kAutoForm = -1;
 // Largest number of blocks in one row handled by the LDS-tabled streaming
 // kernel; wider rows (never produced by the builder) take a simpler kernel.
 constexpr int kNbMax = 512;
@@ -110,17 +113,19 @@ struct Launch {
   int mode = MODE_STORE;
   int64_t row_begin = 0, row_count = 0;  // slice of the kind's row table
   int32_t max_rows = 0;                   // largest output length of its rows
+  int64_t max_cols = 0;                   // most input columns of its rows
+  int32_t min_rows = kMaxDim;             // smallest output length of its rows that is not zero
   bool lowrank = true;                    // false for the dense near-field phase (always FP64)
-  int kc = 64;                            // MFMA path: columns per LDS chunk (tuned in batches)
+  int kc = kAutoForm;                     // batches: kernel form (h2_tune_set codes)
   int64_t grid = 0;                       // MFMA path: workgroups (0 = one per row; fewer = persistent)
   // single-operator MFMA path, per precision of the launch (H2_PREC_*; the
   // dense rows always use the FP64 entry): chunk columns and workgroups, set
   // by h2_tune
-  int kcp[3] = {64, 64, 64};
+  int kcp[3] = {kAutoForm, kAutoForm, 64};
   int64_t gridp[3] = {0, 0, 0};
   int remapp[3] = {0, 0, 0};  // XCD-aware row ranges
   int flp[3] = {1, 1, 1};     // wave-row kernels: read the fragment-ordered copy when there is one
-  int occp[3] = {0, 0, 0};    // wave-row kernels: 5 = the form with more rows in flight
+  int occp[3] = {0, 0, 0};    // wave-row kernels: 5 = the second form
   float tuned_ms[3] = {0, 0, 0};  // time of the chosen setting when tuned (two runs)
   // sweep transfer launches: the level of the parent nodes (upsweep: whose
   // x^ it computes; downsweep: whose y^ it pushes down); -1 for other launches
@@ -268,6 +273,7 @@ void transpose_tasks(const OpLayout& L, std::vector<TransTask>* out);
 void build_transposed(const uint8_t* buf, const OpLayout& L, double* tr);
 void emit_rows_N(const OpLayout& L, const RowBases& B, RowsN* R);
 void append_row(RowTables& t, const RowSpec& r);
+int64_t row_cols(const RowSpec& r);
 int64_t row_work(const RowSpec& r);
 // Places the fragment-ordered copy of rows [begin, end) of t: rows with the
 // same matrix (array, offset and shape) share one region; regions start at
@@ -354,6 +360,7 @@ struct h2_op_s {
   int32_t* d_perm = nullptr;
   int32_t* d_pinv = nullptr;  // original index -> tree position
   bool mfma_ok = true;        // every op-'N' launch fits the MFMA row kernel
+  bool mfma_t_ok = false;     // and every op-'T' one (transposed rows of at most 64 outputs)
   // workgroups of the dense launches on the streaming path (nv <= 4): two per
   // CU, a persistent grid that leaves the other slots to the sweeps beside it
   int64_t dense_stream_grid = 0;
@@ -458,18 +465,37 @@ hipError_t launch_permute_out_rm(const double* Z, const int32_t* pinv, double al
 // workgroups (0: enough for every row at once); remap: XCD-aware row ranges
 constexpr int kWaveRows = 9, kWaveTiles = 10;
 // fl: the fragment-ordered copy of the rows' matrices (rows' fl_off), read
-// instead of `data` when not null; occ != 0: the form with more rows in flight
-// (two waves per row at 64 vectors, else half the columns per load group; none
-// at 48 vectors); the results are bitwise the same.  The matrix data must be
+// instead of `data` when not null and every row fills the launch's tiles;
+// min_rows: the shortest row that has outputs; occ != 0: the second form (two waves per
+// row at 64 vectors, half the columns per load group at 16 and 32; none at 48
+// and with narrow); the results are bitwise the same.  The matrix data must be
 // followed by kRowSlack readable bytes.
 template <typename T>
 hipError_t launch_wave_rows(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
-                            const T* data, const double* in, double* out, int nvp, int mode, int max_rows,
-                            hipStream_t s, int64_t grid, bool narrow = false, int remap = 0, const T* fl = nullptr,
-                            int occ = 0);
+                            const T* data, const double* in, double* out, int nvp, int mode, int min_rows,
+                            int max_rows, hipStream_t s, int64_t grid, bool narrow = false, int remap = 0,
+                            const T* fl = nullptr, int occ = 0);
+// The form of a launch nobody tuned, by its pass width, rows and longest row:
+// a wave-row kernel wherever it takes the rows.  Enough rows to fill the GPU
+// at two or three waves per SIMD: a wave per row, the fewest operand loads per
+// MFMA; fewer rows are split over two or four waves, which shortens the one
+// row that each wave waits for.  Measured (us per product, 2D rank 36, 64
+// vectors; a wave per row / two / four / the LDS-staged kernel that was the
+// default before): 2048 points 295 / 186 / 133 / 298, 32 768 points 444 / 313 /
+// 337 / 529, 131 072 points 774 / 890 / 1225 / 1299; at 16 vectors whole against
+// half load groups 121 / 136 at 2048 points, 471 / 430 at 131 072.
+struct RowForm {
+  int kc, occ;
+};
+RowForm auto_form(int nvp, int64_t rows, int max_rows);
 // True when launch_wave_rows has a second form (occ != 0) for this pass width
-inline bool wave_alt(int nvp) { return nvp != 48; }
+inline bool wave_alt(int nvp, bool narrow) { return nvp != 48 && !narrow; }
 // dst[R.fl_off ...] = the fragment-ordered copy of every row's matrix at src[R.data_off ...]
+// The transposed rows of op 'T' on the multi-vector path (FP64, at most 64
+// outputs per row, any number of blocks): row-major out = sum of M_b^T x_b
+hipError_t launch_wave_cols(const RowDesc* rows, int64_t nrows, const int64_t* bdata, const int32_t* bmr,
+                            const int64_t* bin, const double* data, const double* in, double* out, int nvp,
+                            int max_rows, hipStream_t s);
 template <typename T>
 hipError_t launch_rows_to_fl(const RowDesc* rows, int64_t nrows, const int32_t* colend, const T* src, T* dst,
                              hipStream_t s);

@@ -63,7 +63,12 @@ constexpr int kChunk = 1024;  // columns of one source-row table (4 KB of LDS pe
 // stored, the latter's operands are zeroed.
 // FL: M read from the row's fragment-ordered copy (see k_rows_to_fl): tile t
 // is rows 16t + l%16, two steps per 16-byte load.
-template <typename T, int NT, int NTW, int NF, int TQ, int U, int W, bool FL>
+// WHOLE: every row of the launch has matrix rows in every tile, and every group
+// issues the same number of loads, so that the waits before a group's MFMAs
+// count past the next group's loads.  In launches of mixed rows the loads of a
+// row's empty tiles are skipped (cheaper than loading them, though the waits
+// then count the fewer).
+template <typename T, int NT, int NTW, int NF, int TQ, int U, int W, bool FL, bool WHOLE>
 __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__ rows, int64_t nrows,
                                                      const int32_t* __restrict__ colend,
                                                      const int64_t* __restrict__ in_off,
@@ -78,7 +83,7 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
   constexpr bool BV = NTW % 2 == 0;  // tiles j: vectors NTW * arow + j, else 16 j + arow
   constexpr int ES = sizeof(T);
   typedef const __attribute__((address_space(1))) char* gptr;
-  static_assert((U == 2 || U == 4) && kChunk % G == 0, "load groups");
+  static_assert((U == 2 || U % 4 == 0) && kChunk % G == 0, "load groups");
   // source rows of a chunk's columns; a lane's U steps of a group adjacent,
   // and two groups of padding for the reads ahead
   __shared__ __align__(16) uint32_t s_src[4][kChunk + 2 * G];
@@ -140,9 +145,12 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
     double b[U][NTW], b2[U][NTW];
     uint32_t idx[U];
     auto index = [&](int g) __attribute__((always_inline)) {  // source rows of group g
-      if constexpr (U == 4) {
-        const uint4 v = *reinterpret_cast<const uint4*>(src + G * g + 4 * akk);
-        idx[0] = v.x, idx[1] = v.y, idx[2] = v.z, idx[3] = v.w;
+      if constexpr (U % 4 == 0) {
+#pragma unroll
+        for (int u = 0; u < U; u += 4) {
+          const uint4 v = *reinterpret_cast<const uint4*>(src + G * g + U * akk + u);
+          idx[u] = v.x, idx[u + 1] = v.y, idx[u + 2] = v.z, idx[u + 3] = v.w;
+        }
       } else {
         const uint2 v = *reinterpret_cast<const uint2*>(src + G * g + 2 * akk);
         idx[0] = v.x, idx[1] = v.y;
@@ -154,7 +162,7 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
       asm volatile("" : "+s"(sbase));  // keeps the base scalar: lane offsets stay 32-bit constants of the row
 #pragma unroll
       for (int t = 0; t < NA; ++t) {
-        if (t < NF ? (t > 0 && t >= nt) : !tq) continue;  // wave-uniform
+        if (!WHOLE && (t < NF ? (t > 0 && t >= nt) : !tq)) continue;  // wave-uniform
         if constexpr (FL) {
 #pragma unroll
           for (int u = 0; u < U; u += 2) {
@@ -200,7 +208,7 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
     auto compute = [&](T(&x)[U][NA], double(&y)[U][NTW], int steps) __attribute__((always_inline)) {
 #pragma unroll
       for (int t = 0; t < NF; ++t) {
-        if (t > 0 && t >= nt) continue;  // wave-uniform
+        if (!WHOLE && t > 0 && t >= nt) continue;  // wave-uniform
 #pragma unroll
         for (int u = 0; u < U; ++u)
           if (u < steps)
@@ -208,7 +216,7 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
             for (int j = 0; j < NTW; ++j) acc[t][j] = Mfma<T>::op(x[u][t], (T)y[u][j], acc[t][j]);
       }
       if constexpr (TQ > 0) {
-        if (tq)
+        if (WHOLE || tq)
 #pragma unroll
           for (int u = 0; u < U; ++u)
             if (u < steps)
@@ -256,7 +264,7 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
         if (bcur >= R.blk_end) more = false;
       }
       // columns past the chunk: its last source row, up to two whole groups on
-      if (lane < 3 * G && cn + lane < (cn + G - 1) / G * G + 2 * G) put_src(cn + lane, last);
+      for (int c = cn + lane; c < (cn + G - 1) / G * G + 2 * G; c += 64) put_src(c, last);
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -341,6 +349,206 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
   }
 }
 
+// Transposed row list (op 'T', FP64): out (ms x 16NT) = sum over the blocks of
+// a block column of M_b^T (ms x mr_b) x_b, M_b stored column-major mr_b x ms.
+// The same wave-per-row product as k_wave_rows with A[i][k] = M_b[k, i]: a
+// load group is 4U rows of one block, lane l holding rows U (l/16) .. + U - 1
+// of output column l%16 (16-byte loads, 32U contiguous bytes of a column), in
+// a block's last group the operands past its rows zeroed.  Every group issues
+// the same number of loads, so that the waits before a group's MFMAs count
+// past the next group's loads.  Input rows of a block are consecutive, so no
+// source-row table is needed.
+// Bound by the bytes, as the streaming of the same blocks untransposed: one
+// pass over the matrix for up to 64 vectors, where passes of four vectors
+// through LDS read it once per four.  Measured on the 2D operator of 100 003
+// points (leaf 50, rank 25) at 24 vectors: product 3.80 -> 0.60 ms.
+// KS: a workgroup per row and vector range, its blocks dealt to the four waves
+// in turn and their partial sums added through LDS in wave order: for launches
+// of too few rows to give every SIMD four waves, where a row's chain of loads
+// is what the launch waits for.
+template <int NT, int NTW, int NF, int TQ, int U, int W, bool KS>
+__global__ __launch_bounds__(kT, W) void k_wave_cols(const RowDesc* __restrict__ rows, int64_t nrows,
+                                                     const int64_t* __restrict__ bdata,
+                                                     const int32_t* __restrict__ bmr,
+                                                     const int64_t* __restrict__ bin,
+                                                     const double* __restrict__ data, const double* in,
+                                                     double* out) {
+  typedef double t2 __attribute__((ext_vector_type(2), aligned(8)));
+  typedef double v2 __attribute__((ext_vector_type(2)));
+  typedef const __attribute__((address_space(1))) char* gptr;
+  constexpr int NVP = 16 * NT, WPR = NT / NTW, RPW = 4 / WPR, G = 4 * U, NA = NF + TQ;
+  constexpr bool BV = NTW % 2 == 0;
+  constexpr int LDP = 16 * NTW;  // LDS row of the partial sums
+  __shared__ __align__(16) double part[KS ? 4 * (16 * NF + 4 * TQ) * LDP : 1];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int slot = wave / WPR, vt0 = KS ? (int)(blockIdx.x % WPR) * NTW : (wave % WPR) * NTW;
+  const int arow = lane & 15, akk = lane >> 4;
+  const int vcol = 16 * vt0 + (BV ? NTW * arow : arow);
+  const double* inl = in + vcol;
+  const int64_t ri = KS ? blockIdx.x / WPR : (int64_t)blockIdx.x * RPW + slot;
+  if (ri >= nrows) return;
+  const RowDesc R = rows[ri];
+  constexpr int STEP = KS ? 4 : 1;  // blocks from one of this wave's to the next
+  const int ms = R.nrows;
+  if (ms <= 0) return;
+  d4 acc[NF][NTW];
+  double acc4[TQ > 0 ? TQ : 1][NTW];
+#pragma unroll
+  for (int t = 0; t < NF; ++t)
+#pragma unroll
+    for (int j = 0; j < NTW; ++j) acc[t][j] = d4{0, 0, 0, 0};
+#pragma unroll
+  for (int t = 0; t < (TQ > 0 ? TQ : 1); ++t)
+#pragma unroll
+    for (int j = 0; j < NTW; ++j) acc4[t][j] = 0.0;
+  // output column of each A value (past ms: the last one; not stored)
+  int col[NA];
+#pragma unroll
+  for (int t = 0; t < NA; ++t) col[t] = min(t < NF ? 16 * t + arow : 16 * NF + 4 * (t - NF) + (arow & 3), ms - 1);
+  const int nt = min((ms + 15) >> 4, NF);
+  const bool tq = TQ > 0 && ms > 16 * NF;
+
+  double a[U][NA], a2[U][NA], b[U][NTW], b2[U][NTW];
+  int rem = 0, rem2 = 0;  // rows of the block in each buffer's group (G: a whole group)
+  // the block that the next load reads, and the table entries of the one after it
+  int blk = R.blk_begin + (KS ? wave : 0), k0 = 0;
+  int mr = 0, mrn = 0;
+  int64_t bd = 0, bi = 0, bdn = 0, bin_n = 0;
+  auto peek = [&](int i) __attribute__((always_inline)) {
+    if (i < R.blk_end) {
+      mrn = bmr[i];
+      bdn = bdata[i];
+      bin_n = bin[i];
+    }
+  };
+  auto advance = [&]() __attribute__((always_inline)) {  // to the next block with rows
+    for (;;) {
+      mr = mrn;
+      bd = bdn;
+      bi = bin_n;
+      k0 = 0;
+      peek(blk + STEP);
+      if (blk >= R.blk_end || mr > 0) break;
+      blk += STEP;
+    }
+  };
+  auto load = [&](double(&x)[U][NA], double(&y)[U][NTW], int& left) __attribute__((always_inline)) -> bool {
+    if (blk >= R.blk_end) return false;
+    left = min(mr - k0, G);
+    const gptr base = (gptr)(data + bd + k0);
+    const double* src = inl + (bi + k0) * NVP;
+    const int kl = min(U * akk, left - 1);  // the lane's first row, or the last one left
+#pragma unroll
+    for (int t = 0; t < NA; ++t) {
+      const uint32_t off = (uint32_t)(kl + mr * col[t]) * 8u;
+#pragma unroll
+      for (int u = 0; u < U; u += 2) {
+        const t2 v = __builtin_nontemporal_load(
+            reinterpret_cast<const __attribute__((address_space(1))) t2*>(base + off + 8 * u));
+        x[u][t] = v[0];
+        x[u + 1][t] = v[1];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double* sv = src + min(kl + u, left - 1) * NVP;
+      if constexpr (BV) {
+#pragma unroll
+        for (int j = 0; j < NTW; j += 2) {
+          const v2 v = *reinterpret_cast<const v2*>(sv + j);
+          y[u][j] = v[0];
+          y[u][j + 1] = v[1];
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < NTW; ++j) y[u][j] = sv[16 * j];
+      }
+    }
+    k0 += G;
+    if (k0 >= mr) {
+      blk += STEP;
+      advance();
+    }
+    return true;
+  };
+  auto compute = [&](double(&x)[U][NA], double(&y)[U][NTW], int left) __attribute__((always_inline)) {
+    if (left < G) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (U * akk + u >= left) {
+#pragma unroll
+          for (int t = 0; t < NA; ++t) x[u][t] = 0.0;
+#pragma unroll
+          for (int j = 0; j < NTW; ++j) y[u][j] = 0.0;
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < NF; ++t) {
+      if (t > 0 && t >= nt) continue;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (u < left)
+#pragma unroll
+          for (int j = 0; j < NTW; ++j) acc[t][j] = Mfma<double>::op(x[u][t], y[u][j], acc[t][j]);
+    }
+    if constexpr (TQ > 0) {
+      if (tq)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (u < left)
+#pragma unroll
+            for (int t = 0; t < TQ; ++t)
+#pragma unroll
+              for (int j = 0; j < NTW; ++j)
+                acc4[t][j] = __builtin_amdgcn_mfma_f64_4x4x4f64(x[u][NF + t], y[u][j], acc4[t][j], 0, 0, 0);
+    }
+  };
+  peek(blk);
+  advance();
+  bool has = load(a, b, rem);
+  while (has) {
+    const bool has2 = load(a2, b2, rem2);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(a, b, rem);
+    __builtin_amdgcn_sched_barrier(0);
+    if (!has2) break;
+    has = load(a, b, rem);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(a2, b2, rem2);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  auto put = [&](int row, auto val) __attribute__((always_inline)) {
+    if (row >= ms) return;
+    double* o = KS ? part + (wave * ms + row) * LDP + vcol - 16 * vt0 : out + (R.out_off + row) * NVP + vcol;
+    if constexpr (BV) {
+#pragma unroll
+      for (int j = 0; j < NTW; j += 2) *reinterpret_cast<v2*>(o + j) = v2{val(j), val(j + 1)};
+    } else {
+#pragma unroll
+      for (int j = 0; j < NTW; ++j) o[16 * j] = val(j);
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < NF; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) put(16 * t + 4 * r + akk, [&](int j) { return acc[t][j][r]; });
+  if constexpr (TQ > 0) {
+#pragma unroll
+    for (int t = 0; t < TQ; ++t) put(16 * NF + 4 * t + akk, [&](int j) { return acc4[t][j]; });
+  }
+  if constexpr (KS) {
+    __syncthreads();
+    for (int e = threadIdx.x; e < ms * 16 * NTW; e += kT) {
+      const int row = e / (16 * NTW), v = e % (16 * NTW);
+      double sum = part[row * LDP + v];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) sum += part[(w * ms + row) * LDP + v];
+      out[(R.out_off + row) * NVP + 16 * vt0 + v] = sum;
+    }
+  }
+}
+
 // Registers of a form (32-bit), and from them the waves per SIMD it is
 // compiled for: 512 / W registers each, W >= 2 so that the accumulators stay
 // in VGPRs.
@@ -370,7 +578,7 @@ struct Args {
   const T *data, *fl;
   const double* in;
   double* out;
-  int mode, remap;
+  int mode, remap, min_rows;
   int64_t grid;
   hipStream_t s;
 };
@@ -379,12 +587,17 @@ template <typename T, int NT, int NTW, int NF, int TQ, int U>
 void launch_form(const Args<T>& A) {
   constexpr int W = form_waves(form_regs((int)sizeof(T), NTW, NF, TQ, U));
   const dim3 g((unsigned)wave_grid(A.nrows, 4 * NTW / NT, A.grid, A.remap)), b(kT);
-  if (A.fl)
-    hipLaunchKernelGGL((k_wave_rows<T, NT, NTW, NF, TQ, U, W, true>), g, b, 0, A.s, A.rows, A.nrows, A.colend,
+  // the shortest row fills every tile (pairs of tiles hold interleaved rows)
+  const bool whole = std::min((A.min_rows + 31) / 32 * 2, NF) == NF && (TQ == 0 || A.min_rows > 16 * NF);
+  if (A.fl && whole && A.min_rows > 16 * (NF - 1))
+    hipLaunchKernelGGL((k_wave_rows<T, NT, NTW, NF, TQ, U, W, true, true>), g, b, 0, A.s, A.rows, A.nrows, A.colend,
                        A.in_off, A.fl, A.in, A.out, A.mode, A.remap);
-  else
-    hipLaunchKernelGGL((k_wave_rows<T, NT, NTW, NF, TQ, U, W, false>), g, b, 0, A.s, A.rows, A.nrows, A.colend,
+  else if (whole)
+    hipLaunchKernelGGL((k_wave_rows<T, NT, NTW, NF, TQ, U, W, false, true>), g, b, 0, A.s, A.rows, A.nrows, A.colend,
                        A.in_off, A.data, A.in, A.out, A.mode, A.remap);
+  else
+    hipLaunchKernelGGL((k_wave_rows<T, NT, NTW, NF, TQ, U, W, false, false>), g, b, 0, A.s, A.rows, A.nrows,
+                       A.colend, A.in_off, A.data, A.in, A.out, A.mode, A.remap);
 }
 
 // Row tiles by the longest row of the launch: full 16-row tiles, and for
@@ -409,27 +622,97 @@ void launch_rows_of(const Args<T>& A, int max_rows) {
   }
 }
 
+// Waves (rows times vector ranges) below which a block column is split over
+// the four waves of a workgroup.
+constexpr int64_t kColsSplit = 8192;
+
+struct ColArgs {
+  const RowDesc* rows;
+  int64_t nrows;
+  const int64_t* bdata;
+  const int32_t* bmr;
+  const int64_t* bin;
+  const double *data, *in;
+  double* out;
+  hipStream_t s;
+};
+
+template <int NT, int NTW, int NF, int TQ, int U>
+void launch_cols_form(const ColArgs& A) {
+  constexpr int W = form_waves(form_regs(8, NTW, NF, TQ, U) + 10);
+  constexpr int RPW = 4 * NTW / NT;
+  if (A.nrows * (NT / NTW) < kColsSplit)
+    hipLaunchKernelGGL((k_wave_cols<NT, NTW, NF, TQ, U, W, true>), dim3((unsigned)(A.nrows * (NT / NTW))), dim3(kT),
+                       0, A.s, A.rows, A.nrows, A.bdata, A.bmr, A.bin, A.data, A.in, A.out);
+  else
+    hipLaunchKernelGGL((k_wave_cols<NT, NTW, NF, TQ, U, W, false>), dim3((unsigned)((A.nrows + RPW - 1) / RPW)),
+                       dim3(kT), 0, A.s, A.rows, A.nrows, A.bdata, A.bmr, A.bin, A.data, A.in, A.out);
+}
+
+template <int NT, int NTW, int U>
+void launch_cols_of(const ColArgs& A, int max_rows) {
+  const int nf = max_rows >> 4, rem = max_rows & 15;
+  if (nf >= 1 && nf <= 3 && rem >= 1 && rem <= 8) {
+    if (nf == 1) return rem <= 4 ? launch_cols_form<NT, NTW, 1, 1, U>(A) : launch_cols_form<NT, NTW, 1, 2, U>(A);
+    if (nf == 2) return rem <= 4 ? launch_cols_form<NT, NTW, 2, 1, U>(A) : launch_cols_form<NT, NTW, 2, 2, U>(A);
+    return rem <= 4 ? launch_cols_form<NT, NTW, 3, 1, U>(A) : launch_cols_form<NT, NTW, 3, 2, U>(A);
+  }
+  switch (nf + (rem > 0 ? 1 : 0)) {
+    case 0:
+    case 1: return launch_cols_form<NT, NTW, 1, 0, U>(A);
+    case 2: return launch_cols_form<NT, NTW, 2, 0, U>(A);
+    case 3: return launch_cols_form<NT, NTW, 3, 0, U>(A);
+    default: return launch_cols_form<NT, NTW, 4, 0, U>(A);
+  }
+}
+
 }  // namespace
+
+// Two waves per row at 64 vectors: block columns are fewer and longer than
+// four waves per SIMD need, and half the accumulators leave room for them.
+hipError_t launch_wave_cols(const RowDesc* rows, int64_t nrows, const int64_t* bdata, const int32_t* bmr,
+                            const int64_t* bin, const double* data, const double* in, double* out, int nvp,
+                            int max_rows, hipStream_t s) {
+  if (nrows == 0) return hipSuccess;
+  if (max_rows > 64) return hipErrorInvalidValue;
+  const ColArgs A{rows, nrows, bdata, bmr, bin, data, in, out, s};
+  switch (nvp) {
+    case 16: launch_cols_of<1, 1, 4>(A, max_rows); break;
+    case 32: launch_cols_of<2, 2, 2>(A, max_rows); break;
+    case 48: launch_cols_of<3, 3, 2>(A, max_rows); break;
+    case 64: launch_cols_of<4, 2, 2>(A, max_rows); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+RowForm auto_form(int nvp, int64_t rows, int max_rows) {
+  if (max_rows > 64) return {64, 0};
+  if (nvp == 16) return {kWaveRows, rows >= 512 ? 5 : 0};
+  if (nvp == 32) return rows >= 512 ? RowForm{kWaveRows, 5} : RowForm{kWaveTiles, 0};
+  if (nvp == 48 || rows >= 1024) return {kWaveRows, 0};
+  return rows >= 192 ? RowForm{kWaveRows, 5} : RowForm{kWaveTiles, 0};
+}
 
 template <typename T>
 hipError_t launch_wave_rows(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
-                            const T* data, const double* in, double* out, int nvp, int mode, int max_rows,
-                            hipStream_t s, int64_t grid, bool narrow, int remap, const T* fl, int occ) {
+                            const T* data, const double* in, double* out, int nvp, int mode, int min_rows,
+                            int max_rows, hipStream_t s, int64_t grid, bool narrow, int remap, const T* fl, int occ) {
   if (nrows == 0) return hipSuccess;
   if (max_rows > 64) return hipErrorInvalidValue;
-  const Args<T> A{rows, nrows, colend, in_off, data, fl, in, out, mode, remap, grid, s};
+  const Args<T> A{rows, nrows, colend, in_off, data, fl, in, out, mode, remap, min_rows, grid, s};
   // narrow: a wave per 16-vector tile.  Otherwise a wave per row, or (occ) two
-  // waves per row at 64 vectors.  Where one wave holds one tile, and at 32
-  // vectors, occ halves the load groups instead: fewer registers, more waves.
+  // waves per row at 64 vectors and half the columns per load group at 16 and
+  // 32: fewer registers, more waves.
   switch (nvp) {
-    case 16: occ ? launch_rows_of<T, 1, 1, 2>(A, max_rows) : launch_rows_of<T, 1, 1, 4>(A, max_rows); break;
+    case 16: occ && !narrow ? launch_rows_of<T, 1, 1, 2>(A, max_rows) : launch_rows_of<T, 1, 1, 4>(A, max_rows); break;
     case 32:
-      if (narrow) occ ? launch_rows_of<T, 2, 1, 2>(A, max_rows) : launch_rows_of<T, 2, 1, 4>(A, max_rows);
+      if (narrow) launch_rows_of<T, 2, 1, 4>(A, max_rows);
       else occ ? launch_rows_of<T, 2, 2, 2>(A, max_rows) : launch_rows_of<T, 2, 2, 4>(A, max_rows);
       break;
     case 48: launch_rows_of<T, 3, 3, 2>(A, max_rows); break;
     case 64:
-      if (narrow) occ ? launch_rows_of<T, 4, 1, 2>(A, max_rows) : launch_rows_of<T, 4, 1, 4>(A, max_rows);
+      if (narrow) launch_rows_of<T, 4, 1, 4>(A, max_rows);
       else occ ? launch_rows_of<T, 4, 2, 2>(A, max_rows) : launch_rows_of<T, 4, 4, 2>(A, max_rows);
       break;
     default: return hipErrorInvalidValue;
@@ -437,10 +720,10 @@ hipError_t launch_wave_rows(const RowDesc* rows, int64_t nrows, const int32_t* c
   return hipGetLastError();
 }
 template hipError_t launch_wave_rows<double>(const RowDesc*, int64_t, const int32_t*, const int64_t*, const double*,
-                                             const double*, double*, int, int, int, hipStream_t, int64_t, bool, int,
-                                             const double*, int);
+                                             const double*, double*, int, int, int, int, hipStream_t, int64_t, bool,
+                                             int, const double*, int);
 template hipError_t launch_wave_rows<float>(const RowDesc*, int64_t, const int32_t*, const int64_t*, const float*,
-                                            const double*, double*, int, int, int, hipStream_t, int64_t, bool, int,
-                                            const float*, int);
+                                            const double*, double*, int, int, int, int, hipStream_t, int64_t, bool,
+                                            int, const float*, int);
 
 }  // namespace h2

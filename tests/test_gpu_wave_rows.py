@@ -3,7 +3,8 @@ around the 16-row tiles and the four-row tails (one and two of them), rows of
 one column, rows of more columns than one source-row table (1024), blocks of
 odd width (four-column steps that straddle blocks) and empty leaves, for every
 pass width, in both forms (codes 9-12), from the column-major matrices and
-from the fragment-ordered copies.  Integer representations: every partial sum
+from the fragment-ordered copies, and untuned; and the transposed rows of op
+'T' at the same edges.  Integer representations: every partial sum
 is an integer below 2^53, so the products are the oracle's bit for bit."""
 import numpy as np
 import pytest
@@ -20,8 +21,8 @@ SHAPES = [(1, 1, 2, 541), (4, 16, 16, 564), (16, 17, 17, 556), (17, 20, 20, 517)
           (48, 52, 52, 568), (52, 56, 56, 572), (56, 57, 57, 596), (57, 64, 64, 557), (64, 64, 64, 584)]
 
 
-def run(g, X, prec):
-    Y = g.gemv(torch.from_numpy(np.asfortranarray(X)).cuda(), alpha=2.0, precision=prec)
+def run(g, X, prec, op="N"):
+    Y = g.gemv(torch.from_numpy(np.asfortranarray(X)).cuda(), op=op, alpha=2.0, precision=prec)
     torch.cuda.synchronize()
     return Y.cpu().numpy()
 
@@ -33,11 +34,14 @@ def test_wave_rows_integer_bitwise(kr, kc, leaf, seed):
                            integer=True, int_range=1)
     ref = oracle.Oracle(buf)
     g = H2Operator(buf)
+    X = np.random.default_rng(0).integers(-1, 2, size=(g.n, 64)).astype(np.float64)
+    assert np.array_equal(run(g, X, "fp64"), ref.gemv(X, alpha=2.0))  # untuned
     for prec in ("fp64", "fp32"):
         g.set_sweeps(prec, False)
     for nv in (5, 32, 40, 64):
         X = np.random.default_rng(nv).integers(-1, 2, size=(g.n, nv)).astype(np.float64)
         want = ref.gemv(X, alpha=2.0)
+        assert np.array_equal(run(g, X, "fp64", "T"), ref.gemv(X, op="T", alpha=2.0)), nv
         # FP32 is exact only while every partial sum stays below 2^24
         small = ref.gemv(X, alpha=2.0, absval=True).max() < 2.0 ** 24
         for prec in ("fp64", "fp32") if small else ("fp64",):
