@@ -259,6 +259,45 @@ bool build_tree_groups(h2_op_s* h, const Parsed& P, const OpLayout& lay, std::ve
   return true;
 }
 
+// The composed sweeps of one op into its plan.  The rows of a stage of one
+// level are those of the per-level sweeps.
+int add_composed(h2_op_s* h, const Composed& C, Plan& plan) {
+  auto stage = [&](const std::vector<RowSpec>& rows, bool split, bool up, int in, int out, int mode,
+                   std::vector<Launch>& dst) {
+    const size_t first = dst.size();
+    add_stream_phase(h, rows, split || up ? ARR_TRANS : ARR_MAT, in, out, mode, split, dst);
+    for (size_t i = first; i < dst.size(); ++i) dst[i].split = split;
+  };
+  for (size_t i = 0; i < C.up.size(); ++i)
+    stage(C.up[i], C.up_split[i] != 0, true, i == 0 ? BUF_XT : BUF_XH, BUF_XH, MODE_STORE, plan.upc);
+  for (size_t i = 0; i < C.down.size(); ++i)
+    stage(C.down[i], C.down_split[i] != 0, false, BUF_YH, BUF_YH, MODE_ACCUM, plan.downc);
+  std::vector<Launch> outl;
+  stage(C.out, C.out_split, false, BUF_YH, BUF_ZN, MODE_FINAL, outl);
+  if (outl.size() != 1) {
+    set_error("internal: composed leaf expansion schedule");
+    return H2_EUNSUPPORTED;
+  }
+  plan.outc = outl[0];
+  return H2_OK;
+}
+
+// Every op-'N' launch list that the fragment-ordered copies and the fixed
+// settings cover.
+std::vector<std::vector<Launch>*> lowrank_lists(Plan& p) {
+  return {&p.up, &p.upc, &p.couple, &p.down, &p.downc, &p.couple_loc, &p.couple_deep, &p.couple_rest};
+}
+std::vector<std::vector<Launch>*> dense_lists(Plan& p) { return {&p.dense, &p.dense2, &p.dense_loc, &p.dense2_loc}; }
+template <class F>
+void each_launch(Plan& p, F f) {
+  for (auto* v : lowrank_lists(p))
+    for (Launch& L : *v) f(L);
+  for (auto* v : dense_lists(p))
+    for (Launch& L : *v) f(L);
+  f(p.out);
+  f(p.outc);
+}
+
 // Build plans and upload; the handle's device is current.
 int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* d_dense) {
   const int64_t q = P.q, n = P.n;
@@ -364,6 +403,23 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
     }
     plan.out = outl[0];
   }
+  // ---- composed sweeps of both ops (a shared basis serves both with the same
+  // rows); their matrices follow the transposed bases
+  Composed cn, ct;
+  {
+    RowBases B;
+    B.ld_x = n;
+    B.ld_h = H;
+    compose_sweeps(lay, B, false, ntrans, true, &cn);
+    if (!composed_fits(cn)) compose_sweeps(lay, B, false, ntrans, false, &cn);
+    if (!h->shared) {
+      compose_sweeps(lay, B, true, cn.ntrans, true, &ct);
+      if (!composed_fits(ct)) compose_sweeps(lay, B, true, cn.ntrans, false, &ct);
+    }
+    int rc;
+    if ((rc = add_composed(h, cn, h->planN)) || (rc = add_composed(h, h->shared ? cn : ct, h->planT))) return rc;
+  }
+  const int64_t ntrans_all = h->shared ? cn.ntrans : ct.ntrans;
   std::vector<int2> tree_ranges;
   h->tree_ok = build_tree_groups(h, P, lay, &tree_ranges);
   if (!h->tree_ok) {
@@ -501,11 +557,12 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
   }
   // ---- transposed copies of the bases (for the upsweep products), made on
   // the device from the uploaded matrix data
-  if (ntrans > 0) {
+  if (ntrans_all > 0) {
     std::vector<TransTask> tasks;
     transpose_tasks(lay, &tasks);
-    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&h->d_trans), ntrans * sizeof(double) + kRowSlack), "hipMalloc(trans)");
-    HIP_TRY(hipMemset(h->d_trans, 0, ntrans * sizeof(double)), "hipMemset(trans)");
+    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&h->d_trans), ntrans_all * sizeof(double) + kRowSlack),
+            "hipMalloc(trans)");
+    HIP_TRY(hipMemset(h->d_trans, 0, ntrans_all * sizeof(double)), "hipMemset(trans)");
     if (!tasks.empty()) {
       TransTask* d_tasks = nullptr;
       HIP_TRY(hipMalloc(reinterpret_cast<void**>(&d_tasks), sizeof(TransTask) * tasks.size()), "hipMalloc(tasks)");
@@ -515,6 +572,8 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
       (void)hipFree(d_tasks);
       if (e != hipSuccess) return hip_fail(e, "transposed basis copies");
     }
+    int rc;
+    if ((rc = run_compose(cn, h->d_mat, h->d_trans)) || (rc = run_compose(ct, h->d_mat, h->d_trans))) return rc;
   }
   h->prefix.assign((size_t)(P.off_U + 7) / 8, 0);
   std::memcpy(h->prefix.data(), buf, (size_t)P.off_U);
@@ -526,18 +585,20 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
   }
   for (const auto* v : {&h->planN.up, &h->planN.couple, &h->planN.down, &h->planN.dense, &h->planN.dense2,
                         &h->planN.couple_loc, &h->planN.dense_loc, &h->planN.dense2_loc, &h->planN.couple_deep,
-                        &h->planN.couple_rest})
+                        &h->planN.couple_rest, &h->planN.upc, &h->planN.downc})
     for (const Launch& L : *v)
       if (L.kind != KIND_STREAM) h->mfma_ok = false;
   // op 'T': its rows have no fragment-ordered copies, and its transposed rows
   // take the multi-vector kernel up to 64 outputs
   h->mfma_t_ok = h->mfma_ok;
-  for (auto* v : {&h->planT.up, &h->planT.couple, &h->planT.down, &h->planT.dense, &h->planT.dense2})
+  for (auto* v : {&h->planT.up, &h->planT.couple, &h->planT.down, &h->planT.dense, &h->planT.dense2, &h->planT.upc,
+                  &h->planT.downc})
     for (Launch& L : *v) {
       for (int& f : L.flp) f = 0;
       if (L.kind == KIND_WIDE || (L.kind == KIND_GATHER && L.max_rows > 64)) h->mfma_t_ok = false;
     }
   for (int& f : h->planT.out.flp) f = 0;
+  for (int& f : h->planT.outc.flp) f = 0;
   if (h->planT.out.kind != KIND_STREAM) h->mfma_t_ok = false;
   int64_t ib = 0;
   int rc;
@@ -550,7 +611,7 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
       (rc = upload(h->gt.in_off, &h->gt.d_in_off, &ib)) || (rc = upload(tree_ranges, &h->d_tree_ranges, &ib)))
     return rc;
   h->index_bytes = ib;
-  h->stats.device_bytes = mat_bytes + ntrans * (int64_t)sizeof(double) + ib;
+  h->stats.device_bytes = mat_bytes + ntrans_all * (int64_t)sizeof(double) + ib;
   return H2_OK;
 }
 
@@ -665,16 +726,19 @@ int run_launch(h2_op_s* h, const Workspace& w, const Launch& L, int nv, const Ep
   int kcw = L.kcp[lowp ? H2_PREC_FP32 : H2_PREC_FP64], occ = L.occp[lowp ? H2_PREC_FP32 : H2_PREC_FP64];
   if (nvp > 0 && kcw == kAutoForm) {
     RowForm f = auto_form(nvp, L.row_count, L.max_rows);
-    // dense rows beside the BF16 sweeps, one vector tile, rows of up to 1024
+    // dense rows beside the BF16 sweeps, one vector tile, rows of up to 1536
     // columns (2D): there the sweeps' chain is what the product waits for, and
     // the LDS-staged kernel leaves it more of the memory (20 000 points 188
     // against 204-219 us, 82 810 points 245 against 270; longer rows, 3D of
     // 32 768 points, 784 against 649)
-    if (!L.lowrank && prec == H2_PREC_BF16 && nvp == 16 && L.max_cols <= 1024) f = {64, 0};
+    if (!L.lowrank && prec == H2_PREC_BF16 && nvp == 16 && L.max_cols <= 1536) f = {64, 0};
     kcw = f.kc;
     occ = f.occ;
   }
-  if (nvp > 0 && L.kind == KIND_GATHER) {
+  if (nvp > 0 && L.split && L.max_rows <= 64) {
+    e = launch_split_rows(h->rt.d_rows + L.row_begin, L.row_count, h->rt.d_colend, h->rt.d_in_off, data, bufs[L.in],
+                          out, nvp, mode, L.max_rows, s);
+  } else if (nvp > 0 && L.kind == KIND_GATHER) {
     e = launch_wave_cols(h->gt.d_rows + L.row_begin, L.row_count, h->gt.d_data, h->gt.d_mr, h->gt.d_in_off, data,
                          bufs[L.in], out, nvp, L.max_rows, s);
   } else if (nvp > 0 && (kcw == kWaveRows || kcw == kWaveTiles) && L.max_rows <= 64) {
@@ -743,18 +807,16 @@ int prepare_f32(h2_op_s* h) {
 int prepare_fl(h2_op_s* h, int prec) {
   std::lock_guard<std::mutex> lock(h->prep_mu);
   if (!h->mfma_ok) return H2_OK;
-  const Plan& p = h->planN;
   if (!h->fl_placed) {
     // the copies' regions, in the rows' fl_off (the device row table is
     // rewritten; nothing runs on the handle meanwhile)
     FlKeys keys;
     keys.reserve(2 * h->rt.rows.size());
     int64_t n_fl = 0;
-    for (const auto* v : {&p.up, &p.couple, &p.down, &p.dense, &p.dense2, &p.couple_loc, &p.dense_loc,
-                          &p.dense2_loc, &p.couple_deep, &p.couple_rest})
-      for (const Launch& L : *v)
-        if (L.kind == KIND_STREAM) place_fl(h->rt, L.row_begin, L.row_begin + L.row_count, L.arr, &keys, &n_fl);
-    place_fl(h->rt, p.out.row_begin, p.out.row_begin + p.out.row_count, p.out.arr, &keys, &n_fl);
+    each_launch(h->planN, [&](Launch& L) {
+      if (L.kind == KIND_STREAM && !L.split)
+        place_fl(h->rt, L.row_begin, L.row_begin + L.row_count, L.arr, &keys, &n_fl);
+    });
     if (!h->rt.rows.empty())
       HIP_TRY(hipMemcpy(h->rt.d_rows, h->rt.rows.data(), sizeof(RowDesc) * h->rt.rows.size(), hipMemcpyHostToDevice),
               "hipMemcpy(row table)");
@@ -767,7 +829,7 @@ int prepare_fl(h2_op_s* h, int prec) {
   auto make = [&](void* d, bool fp32) -> hipError_t {
     hipError_t e = hipSuccess;
     auto one = [&](const Launch& L) {
-      if (e != hipSuccess || (fp32 && !L.lowrank)) return;  // the dense rows stay FP64
+      if (e != hipSuccess || L.split || (fp32 && !L.lowrank)) return;  // the dense rows stay FP64
       if (fp32)
         e = launch_rows_to_fl<float>(h->rt.d_rows + L.row_begin, L.row_count, h->rt.d_colend,
                                      L.arr == ARR_TRANS ? h->d_trans32 : h->d_mat32, static_cast<float*>(d), nullptr);
@@ -775,10 +837,7 @@ int prepare_fl(h2_op_s* h, int prec) {
         e = launch_rows_to_fl<double>(h->rt.d_rows + L.row_begin, L.row_count, h->rt.d_colend,
                                       L.arr == ARR_TRANS ? h->d_trans : h->d_mat, static_cast<double*>(d), nullptr);
     };
-    for (const auto* v : {&p.up, &p.couple, &p.down, &p.dense, &p.dense2, &p.couple_loc, &p.dense_loc,
-                          &p.dense2_loc, &p.couple_deep, &p.couple_rest})
-      for (const Launch& L : *v) one(L);
-    one(p.out);
+    each_launch(h->planN, one);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     return e;
   };
@@ -817,11 +876,7 @@ int drop_unused_fl(h2_op_s* h) {
     use64 = use64 || reads(H2_PREC_FP64);
     use32 = use32 || (L.lowrank && reads(H2_PREC_FP32));
   };
-  const Plan& p = h->planN;
-  for (const auto* v : {&p.up, &p.couple, &p.down, &p.dense, &p.dense2, &p.couple_loc, &p.dense_loc,
-                        &p.dense2_loc, &p.couple_deep, &p.couple_rest})
-    for (const Launch& L : *v) look(L);
-  look(p.out);
+  each_launch(h->planN, look);
   if (!use64 && h->d_fl) {
     HIP_TRY(hipFree(h->d_fl), "hipFree(fragment-ordered copy)");
     h->d_fl = nullptr;
@@ -860,26 +915,33 @@ int prepare_bf16(h2_op_s* h) {
   return H2_OK;
 }
 
-// The fused sweep launches of one direction (multi-vector path, FP64/FP32).
-int run_tree(h2_op_s* h, const Workspace& w, const std::vector<TreeGroup>& groups, int nvp, int prec,
-             hipStream_t s) {
+// The fused sweep launches of one direction (multi-vector path, FP32).
+int run_tree(h2_op_s* h, const Workspace& w, const std::vector<TreeGroup>& groups, int nvp, hipStream_t s) {
   double* const bufs[4] = {w.xt, w.xh, w.yh, w.zx};
   for (const TreeGroup& G : groups) {
     const hipError_t e =
-        prec == H2_PREC_FP32
-            ? launch_tree<float>(h->d_tree_ranges + G.range_off, G.nwg, G.lv, h->rt.d_rows, h->rt.d_colend,
-                                 h->rt.d_in_off, G.trans_data ? h->d_trans32 : h->d_mat32, bufs, nvp, G.max_rows, s)
-            : launch_tree<double>(h->d_tree_ranges + G.range_off, G.nwg, G.lv, h->rt.d_rows, h->rt.d_colend,
-                                  h->rt.d_in_off, G.trans_data ? h->d_trans : h->d_mat, bufs, nvp, G.max_rows, s);
+        launch_tree<float>(h->d_tree_ranges + G.range_off, G.nwg, G.lv, h->rt.d_rows, h->rt.d_colend, h->rt.d_in_off,
+                           G.trans_data ? h->d_trans32 : h->d_mat32, bufs, nvp, G.max_rows, s);
     if (e != hipSuccess) return hip_fail(e, "fused sweep launch");
   }
   return H2_OK;
 }
 
-// Whether a multi-vector pass runs the fused sweeps.
+// Whether a multi-vector pass runs the fused sweeps (FP32: FP64 has the composed stages instead).
 bool use_tree(const h2_op_s* h, const Workspace& w, bool trans, int nvp, int prec) {
   const int pidx = prec == H2_PREC_FP32 ? 1 : prec == H2_PREC_BF16 ? 2 : 0;
-  return nvp > 0 && !trans && prec != H2_PREC_BF16 && h->tree_ok && w.zx != nullptr && h->sweep_fused[pidx] != 0;
+  return nvp > 0 && !trans && prec == H2_PREC_FP32 && h->tree_ok && w.zx != nullptr && h->sweep_fused[pidx] != 0;
+}
+
+// Where the dense rows run when nobody tuned or set it: on operators of few
+// leaves a half of the dense rows does not fill the GPU, and the composed
+// sweeps leave little to overlap with, so all of them go in one launch from
+// the start.  Measured in us, halves against one launch: multi-vector path
+// (16 vectors) 151 / 102 at 8192 points, 305 / 292 at 100 003 (2048 leaves),
+// 871 / 874 at 262 144 (4096 or 8192 leaves); one vector 91 / 59, 114 / 92 at
+// 32 768 (512 leaves), 222 / 231 at 100 003, 315 / 330 at 131 072.
+int sched_of(const h2_op_s* h, int set, bool mfma) {
+  return set != kAutoSched ? set : h->nleaves < (mfma ? 8192 : 2048) ? 2 : 0;
 }
 
 // One pass of the product: nv <= kPassVectors vectors on the streaming path
@@ -891,6 +953,11 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
   const int pidx = prec == H2_PREC_FP32 ? 1 : prec == H2_PREC_BF16 ? 2 : 0;
   const int cm = (!trans && nvp > 0) ? h->couple_mode[pidx] : 0;
   const int dm = (!trans && nvp > 0) ? h->dense_mode[pidx] : 0;
+  // FP64: the sweeps in composed stages
+  const bool comp = prec == H2_PREC_FP64;
+  const std::vector<Launch>& up = comp ? plan.upc : plan.up;
+  const std::vector<Launch>& down = comp ? plan.downc : plan.down;
+  const Launch& outl = comp ? plan.outc : plan.out;
   const std::vector<Launch>& couple = cm == 1 ? plan.couple_loc : plan.couple;
   const std::vector<Launch>& dense1 = dm == 1 ? plan.dense_loc : plan.dense;
   const std::vector<Launch>& dense2 = dm == 1 ? plan.dense2_loc : plan.dense2;
@@ -921,28 +988,40 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
   // and the leaf level's coupling rows on a third stream as soon as the leaf
   // products are done, beside the upper upsweep, the other levels' coupling
   // rows and the upper downsweep (the last downsweep level waits for them).
-  const int sched = trans ? 0 : nvp > 0 ? h->sched[pidx] : h->sched1[pidx];
+  const int sched = sched_of(h, trans ? kAutoSched : nvp > 0 ? h->sched[pidx] : h->sched1[pidx], nvp > 0);
+  // both halves from the start: one launch where their rows are adjacent
+  const bool whole = (sched == 2 || sched == 3) && dense1.size() == 1 && dense2.size() == 1 &&
+                     dense1[0].kind == dense2[0].kind &&
+                     dense1[0].row_begin + dense1[0].row_count == dense2[0].row_begin;
   const bool fused = use_tree(h, w, trans, nvp, prec);
   // FP32 at 64 vectors: the coupling launches gather x^ from an FP32 copy
   const bool x32 = prec == H2_PREC_FP32 && nvp == kPassVectorsMfma && w.xh32;
   // (a workspace without the third stream, such as the no-allocation
   // product's views, takes schedule 2's order instead)
-  const bool split = sched == 3 && !fused && !x32 && !plan.down.empty() && !plan.couple_deep.empty() &&
-                     !plan.up.empty() && w.side2 && w.ev_deep && w.ev_deep_done;
+  const bool split = sched == 3 && !fused && !x32 && !down.empty() && !plan.couple_deep.empty() && !up.empty() &&
+                     w.side2 && w.ev_deep && w.ev_deep_done;
   auto fork_dense1 = [&]() -> int {
     HIP_TRY(hipEventRecord(w.ev_fork, s), "hipEventRecord(fork)");
     HIP_TRY(hipStreamWaitEvent(w.side, w.ev_fork, 0), "hipStreamWaitEvent(fork)");
     STEP(mark(5, w.side));
-    for (const Launch& L : dense1) STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));
+    if (whole) {
+      Launch L = dense1[0];
+      L.row_count += dense2[0].row_count;
+      L.max_rows = std::max(L.max_rows, dense2[0].max_rows);
+      L.min_rows = std::min(L.min_rows, dense2[0].min_rows);
+      L.max_cols = std::max(L.max_cols, dense2[0].max_cols);
+      STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));
+    } else
+      for (const Launch& L : dense1) STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));
     STEP(mark(9, w.side));
     return H2_OK;
   };
   if (sched != 1) STEP(fork_dense1());
   if (fused) {
-    STEP(run_tree(h, w, h->tree_up, nvp, prec, s));
+    STEP(run_tree(h, w, h->tree_up, nvp, s));
   } else {
-    for (size_t i = 0; i < plan.up.size(); ++i) {
-      if (!skipped(h, plan.up[i])) STEP(run_launch(h, w, plan.up[i], nv, ep, s, nvp, -1, prec));
+    for (size_t i = 0; i < up.size(); ++i) {
+      if (!skipped(h, up[i])) STEP(run_launch(h, w, up[i], nv, ep, s, nvp, -1, prec));
       if (split && i == 0) {  // the leaf level's x^ is complete
         HIP_TRY(hipEventRecord(w.ev_deep, s), "hipEventRecord(deep)");
         HIP_TRY(hipStreamWaitEvent(w.side2, w.ev_deep, 0), "hipStreamWaitEvent(deep)");
@@ -968,7 +1047,8 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
     HIP_TRY(hipStreamWaitEvent(w.side, w.ev_mid, 0), "hipStreamWaitEvent(mid)");
   }
   STEP(mark(10, w.side));
-  for (const Launch& L : dense2) STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));
+  if (!whole)
+    for (const Launch& L : dense2) STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));
   STEP(mark(6, w.side));
   HIP_TRY(hipEventRecord(w.ev_join, w.side), "hipEventRecord(join)");
   // Multi-vector path: the leaf expansion U y^ goes to its own buffer w.zx,
@@ -976,15 +1056,15 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
   // permutation adds the dense partial, the same Z + U y^ addition.
   const bool zx = nvp > 0 && w.zx != nullptr;
   if (fused) {
-    STEP(run_tree(h, w, h->tree_down, nvp, prec, s));
+    STEP(run_tree(h, w, h->tree_down, nvp, s));
   } else {
-    for (size_t i = 0; i < plan.down.size(); ++i) {
-      if (split && i + 1 == plan.down.size())  // the leaf level's y^ needs its coupling rows
+    for (size_t i = 0; i < down.size(); ++i) {
+      if (split && i + 1 == down.size())  // the leaf level's y^ needs its coupling rows
         HIP_TRY(hipStreamWaitEvent(s, w.ev_deep_done, 0), "hipStreamWaitEvent(deep done)");
-      if (!skipped(h, plan.down[i])) STEP(run_launch(h, w, plan.down[i], nv, ep, s, nvp, -1, prec));
+      if (!skipped(h, down[i])) STEP(run_launch(h, w, down[i], nv, ep, s, nvp, -1, prec));
     }
   }
-  if (zx && !fused) STEP(run_launch(h, w, plan.out, nv, ep, s, nvp, MODE_STORE, prec, false, w.zx));
+  if (zx && !fused) STEP(run_launch(h, w, outl, nv, ep, s, nvp, MODE_STORE, prec, false, w.zx));
   STEP(mark(4, s));
   HIP_TRY(hipStreamWaitEvent(s, w.ev_join, 0), "hipStreamWaitEvent(join)");
   STEP(mark(7, s));
@@ -993,10 +1073,10 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
     HIP_TRY(launch_permute_out_rm2(w.zn, w.zx, h->d_pinv, alpha, beta, Y, ldy, h->n, nv, nvp, s), "permute out");
   } else if (nvp) {
     // Z += U y^ (into the dense partial), then Y = alpha Z[pinv] + beta Y
-    STEP(run_launch(h, w, plan.out, nv, ep, s, nvp, MODE_ACCUM, prec));
+    STEP(run_launch(h, w, outl, nv, ep, s, nvp, MODE_ACCUM, prec));
     HIP_TRY(launch_permute_out_rm(w.zn, h->d_pinv, alpha, beta, Y, ldy, h->n, nv, nvp, s), "permute out");
   } else {
-    STEP(run_launch(h, w, plan.out, nv, ep, s, 0, -1, prec));
+    STEP(run_launch(h, w, outl, nv, ep, s, 0, -1, prec));
   }
   STEP(mark(8, s));
 #undef STEP
@@ -1438,7 +1518,7 @@ int h2_tune(h2_handle h, int64_t nv, int prec, void* stream) {
   auto tune_list = [&](std::vector<Launch>& v, float* total, bool couple = false) -> int {
     *total = 0.0f;
     for (Launch& L : v) {
-      if (skipped(h, L)) continue;  // never runs
+      if (skipped(h, L) || L.split) continue;  // never runs; one form
       float t = 0.0f;
       const int r = tune_one(L, -1, &t, couple);
       if (r != H2_OK) return r;
@@ -1447,8 +1527,9 @@ int h2_tune(h2_handle h, int64_t nv, int prec, void* stream) {
     return H2_OK;
   };
   float t_up = 0, t_down = 0, t_out = 0, tc = 0, tcl = 0, td1 = 0, td2 = 0, tl1 = 0, tl2 = 0;
-  rc = tune_list(plan.up, &t_up);
-  if (rc == H2_OK) rc = tune_list(plan.down, &t_down);
+  const bool comp = prec == H2_PREC_FP64;  // FP64 runs the composed sweeps
+  rc = tune_list(comp ? plan.upc : plan.up, &t_up);
+  if (rc == H2_OK) rc = tune_list(comp ? plan.downc : plan.down, &t_down);
   if (rc == H2_OK) rc = tune_list(plan.couple, &tc, true);
   if (rc == H2_OK) rc = tune_list(plan.couple_loc, &tcl, true);
   // the split coupling rows of schedule 3 (their times are not compared)
@@ -1459,19 +1540,20 @@ int h2_tune(h2_handle h, int64_t nv, int prec, void* stream) {
   if (rc == H2_OK) rc = tune_list(plan.dense2, &td2);
   if (rc == H2_OK) rc = tune_list(plan.dense_loc, &tl1);
   if (rc == H2_OK) rc = tune_list(plan.dense2_loc, &tl2);
-  if (rc == H2_OK) rc = tune_one(plan.out, w.zx ? MODE_STORE : MODE_ACCUM, &t_out);  // as the product runs it
+  Launch& outl = comp ? plan.outc : plan.out;
+  if (rc == H2_OK && !outl.split) rc = tune_one(outl, w.zx ? MODE_STORE : MODE_ACCUM, &t_out);  // as the product runs it
   if (rc == H2_OK) {
     h->couple_mode[prec] = tcl < tc ? 1 : 0;
     h->dense_mode[prec] = tl1 + tl2 < td1 + td2 ? 1 : 0;
   }
   // fused sweeps (both directions, leaf expansion included) against the tuned
   // per-level launches, two timed runs each after a warm-up
-  if (rc == H2_OK && prec != H2_PREC_BF16 && h->tree_ok && w.zx) {
+  if (rc == H2_OK && prec == H2_PREC_FP32 && h->tree_ok && w.zx) {
     float tf = 0.0f;
     for (int rep = 0; rep < 3 && rc == H2_OK; ++rep) {
       HIP_TRY(hipEventRecord(e0, s), "hipEventRecord");
-      rc = run_tree(h, w, h->tree_up, nvp, prec, s);
-      if (rc == H2_OK) rc = run_tree(h, w, h->tree_down, nvp, prec, s);
+      rc = run_tree(h, w, h->tree_up, nvp, s);
+      if (rc == H2_OK) rc = run_tree(h, w, h->tree_down, nvp, s);
       HIP_TRY(hipEventRecord(e1, s), "hipEventRecord");
       HIP_TRY(hipEventSynchronize(e1), "hipEventSynchronize");
       float ms = 0.0f;
@@ -1543,19 +1625,17 @@ int h2_tune_set(h2_handle h, int prec, int kc, int64_t grid, int xcd, int tree_o
   HIP_TRY(hipDeviceSynchronize(), "hipDeviceSynchronize");
   drop_graphs(h);
   Plan& P = h->planN;
-  for (auto* v : {&P.up, &P.couple, &P.down, &P.couple_loc, &P.couple_deep, &P.couple_rest})
-    for (Launch& L : *v) {
-      L.kcp[prec] = kc;
-      L.gridp[prec] = grid;
-      L.remapp[prec] = xcd ? 1 : 0;
-      L.flp[prec] = 1;
-      L.occp[prec] = occ;
-    }
-  P.out.kcp[prec] = kc;
-  P.out.gridp[prec] = grid;
-  P.out.remapp[prec] = xcd ? 1 : 0;
-  P.out.flp[prec] = 1;
-  P.out.occp[prec] = occ;
+  auto set = [&](Launch& L) {
+    L.kcp[prec] = kc;
+    L.gridp[prec] = grid;
+    L.remapp[prec] = xcd ? 1 : 0;
+    L.flp[prec] = 1;
+    L.occp[prec] = occ;
+  };
+  for (auto* v : lowrank_lists(P))
+    for (Launch& L : *v) set(L);
+  set(P.out);
+  set(P.outc);
   if (prec == H2_PREC_FP64 || kc != 0)  // the dense rows are always FP64
     for (auto* v : {&P.dense, &P.dense2, &P.dense_loc, &P.dense2_loc})
       for (Launch& L : *v) {
@@ -1623,9 +1703,10 @@ int h2_set_fragment_order(h2_handle h, int prec, int enable) {
     if ((rc = h2_prepare(h, prec)) != H2_OK || (rc = prepare_fl(h, prec)) != H2_OK) return rc;
   }
   Plan& P = h->planN;
-  for (auto* v : {&P.up, &P.couple, &P.down, &P.couple_loc, &P.couple_deep, &P.couple_rest})
+  for (auto* v : lowrank_lists(P))
     for (Launch& L : *v) L.flp[prec] = enable ? 1 : 0;
   P.out.flp[prec] = enable ? 1 : 0;
+  P.outc.flp[prec] = enable ? 1 : 0;
   for (auto* v : {&P.dense, &P.dense2, &P.dense_loc, &P.dense2_loc})  // always FP64
     for (Launch& L : *v) L.flp[H2_PREC_FP64] = enable ? 1 : 0;
   return enable ? H2_OK : drop_unused_fl(h);
@@ -1661,16 +1742,19 @@ int h2_plan_info(h2_handle h, char* buf, size_t cap, size_t* needed) {
   };
   for (int p = 0; p < 2; ++p) {
     std::snprintf(line, sizeof line, "%s: sweeps %s (per-level %.3fms, fused %.3fms when tuned)\n", pn[p],
-                  h->tree_ok && h->sweep_fused[p] ? "fused" : "per level", h->sweep_ms[p][0], h->sweep_ms[p][1]);
+                  p == H2_PREC_FP64                  ? "in composed stages"
+                  : h->tree_ok && h->sweep_fused[p] ? "fused"
+                                                    : "per level",
+                  h->sweep_ms[p][0], h->sweep_ms[p][1]);
     t += line;
   }
   for (int p = 0; p < 3; ++p) {
     std::snprintf(line, sizeof line, "%s: dense schedule %d (tuned products %.3f / %.3f / %.3f / %.3f ms)\n",
-                  pn[p], h->sched[p], h->sched_ms[p][0], h->sched_ms[p][1], h->sched_ms[p][2], h->sched_ms[p][3]);
+                  pn[p], sched_of(h, h->sched[p], true), h->sched_ms[p][0], h->sched_ms[p][1], h->sched_ms[p][2], h->sched_ms[p][3]);
     t += line;
     std::snprintf(line, sizeof line,
                   "%s: streaming dense schedule %d (tuned products %.3f / %.3f / %.3f / %.3f ms)\n", pn[p],
-                  h->sched1[p], h->sched1_ms[p][0], h->sched1_ms[p][1], h->sched1_ms[p][2], h->sched1_ms[p][3]);
+                  sched_of(h, h->sched1[p], false), h->sched1_ms[p][0], h->sched1_ms[p][1], h->sched1_ms[p][2], h->sched1_ms[p][3]);
     t += line;
   }
   for (const auto* v : {&h->tree_up, &h->tree_down})
@@ -1680,17 +1764,21 @@ int h2_plan_info(h2_handle h, char* buf, size_t cap, size_t* needed) {
       t += line;
     }
   const Plan& P = h->planN;
-  dump("up", P.up);
+  dump("up", P.upc);
   dump("couple", P.couple);
   dump("couple_deep", P.couple_deep);
   dump("couple_rest", P.couple_rest);
   dump("couple_tree", P.couple_loc);
-  dump("down", P.down);
+  dump("down", P.downc);
   dump("dense1", P.dense);
   dump("dense2", P.dense2);
   dump("dense1_tree", P.dense_loc);
   dump("dense2_tree", P.dense2_loc);
-  dump("out", std::vector<Launch>{P.out});
+  dump("out", std::vector<Launch>{P.outc});
+  // the sweeps level by level: FP32 and BF16
+  dump("level_up", P.up);
+  dump("level_down", P.down);
+  dump("level_out", std::vector<Launch>{P.out});
   *needed = t.size() + 1;
   if (buf && cap > 0) {
     const size_t c = std::min(cap - 1, t.size());

@@ -25,6 +25,7 @@ constexpr int kMaxDim = 256;
 // Kernel form of a multi-vector launch that no tuner or caller set: chosen by
 // auto_form at launch, when the pass width is known.
 constexpr int kAutoForm = -1;
+constexpr int kAutoSched = -1;
 // Largest number of blocks in one row handled by the LDS-tabled streaming
 // kernel; wider rows (never produced by the builder) take a simpler kernel.
 constexpr int kNbMax = 512;
@@ -115,6 +116,7 @@ struct Launch {
   int32_t max_rows = 0;                   // largest output length of its rows
   int64_t max_cols = 0;                   // most input columns of its rows
   int32_t min_rows = kMaxDim;             // smallest output length of its rows that is not zero
+  bool split = false;                     // composed sweep rows of several levels (launch_split_rows on the MFMA path)
   bool lowrank = true;                    // false for the dense near-field phase (always FP64)
   int kc = kAutoForm;                     // batches: kernel form (h2_tune_set codes)
   int64_t grid = 0;                       // MFMA path: workgroups (0 = one per row; fewer = persistent)
@@ -134,6 +136,7 @@ struct Launch {
 
 // The launch sequence of one operation (op 'N' or 'T').
 struct Plan {
+  // the sweeps level by level (FP32 and BF16; the fused sweeps)
   std::vector<Launch> up;      // leaf products, then transfer levels q..1
   std::vector<Launch> couple;  // all levels at once (plus wide rows, if any)
   std::vector<Launch> down;    // transfer levels 1..q
@@ -146,6 +149,9 @@ struct Plan {
   // products of the upsweep) and the other levels', longest first in each
   std::vector<Launch> couple_deep, couple_rest;
   Launch out;                  // leaf expansion + dense partial + alpha/beta update
+  // the sweeps in composed stages (FP64)
+  std::vector<Launch> upc, downc;
+  Launch outc;
 };
 
 // Fused sweeps of the multi-vector path (h2_tree_kernels.hip): the levels
@@ -272,6 +278,31 @@ void transpose_tasks(const OpLayout& L, std::vector<TransTask>* out);
 // The transposed array on the host (zeros where no block lands).
 void build_transposed(const uint8_t* buf, const OpLayout& L, double* tr);
 void emit_rows_N(const OpLayout& L, const RowBases& B, RowsN* R);
+// Composed sweeps (FP64): the transfer levels grouped into stages, each one
+// launch.  An upsweep stage computes x^ of several levels straight from one
+// level below them (or from the points), a downsweep stage adds to y^ of one
+// level (or to the leaf expansion) the parts of several levels above it, with
+// the products of the transfers between them, formed once at load.
+struct ComposeTask {  // dst (m x n) = A (m x k) B (k x n), column-major; k == 0: a copy of A (m x n)
+  int64_t a, b, dst;
+  int32_t m, k, n;
+  int32_t where;  // A in: 0 the matrix array, 1 the transposed array, 2 scratch (as dst: bit 2 set = scratch)
+};
+struct Composed {
+  std::vector<std::vector<RowSpec>> up, down;  // per stage, in running order
+  std::vector<char> up_split, down_split;      // the stage has rows of several levels
+  std::vector<RowSpec> out;                    // leaf expansion
+  bool out_split = false;
+  std::vector<std::vector<ComposeTask>> steps;  // in running order; offsets relative to the operator's arrays
+  std::vector<TransTask> trans;                 // scratch -> transposed array, after the steps
+  int64_t ntrans = 0, nscratch = 0;             // elements of the transposed array (composed rows included) and scratch
+};
+// op 'N' (or 'T': trans_op) rows at the bases B; the composed matrices go to
+// the operator's transposed array from element `first` on.
+// group: false keeps one level per stage.
+void compose_sweeps(const OpLayout& L, const RowBases& B, bool trans_op, int64_t first, bool group, Composed* C);
+// True when every row fits the tabled kernels.
+bool composed_fits(const Composed& C);
 void append_row(RowTables& t, const RowSpec& r);
 int64_t row_cols(const RowSpec& r);
 int64_t row_work(const RowSpec& r);
@@ -386,11 +417,12 @@ struct h2_op_s {
   // the start and the leaf level's coupling rows on a third stream, beside
   // the upsweep above the leaves, the other levels' coupling rows and the
   // downsweep above the leaves
-  int sched[3] = {0, 0, 0};
+  // (kAutoSched until tuned or set: by the operator's size, see sched_of)
+  int sched[3] = {h2::kAutoSched, h2::kAutoSched, h2::kAutoSched};
   float sched_ms[3][4] = {};
   // the same choice for the streaming path (at most 4 vectors per pass; FP64
   // and FP32), tuned separately
-  int sched1[3] = {0, 0, 0};
+  int sched1[3] = {h2::kAutoSched, h2::kAutoSched, h2::kAutoSched};
   float sched1_ms[3][4] = {};
   int64_t index_bytes = 0;
   // the serialized header and index sections (bytes before U), 8-byte aligned,
@@ -449,6 +481,11 @@ hipError_t launch_to_f32(const double* src, float* dst, int64_t n, hipStream_t s
 // task's block of `mat` transposed into `trans` (which the caller zeroed).
 hipError_t launch_transpose_tasks(const TransTask* tasks, int64_t ntasks, const double* mat, double* trans,
                                   hipStream_t s);
+// One step of composed transfers: every task's product (or copy).
+hipError_t launch_compose_tasks(const ComposeTask* tasks, int64_t ntasks, const double* mat, double* trans,
+                                double* scratch, hipStream_t s);
+// Every task list of `C` on the device (synchronous): H2_OK, H2_ENOMEM, H2_EHIP.
+int run_compose(const Composed& C, const double* mat, double* trans);
 // BF16 path (data: __bf16, rows stored row-major; see the kernel file)
 hipError_t launch_rows_mfma_bf16(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
                                  const void* data, const void* in, bool in16, int64_t ldb, void* out, bool out16,
@@ -479,15 +516,21 @@ hipError_t launch_wave_rows(const RowDesc* rows, int64_t nrows, const int32_t* c
 // a wave-row kernel wherever it takes the rows.  Enough rows to fill the GPU
 // at two or three waves per SIMD: a wave per row, the fewest operand loads per
 // MFMA; fewer rows are split over two or four waves, which shortens the one
-// row that each wave waits for.  Measured (us per product, 2D rank 36, 64
-// vectors; a wave per row / two / four / the LDS-staged kernel that was the
-// default before): 2048 points 295 / 186 / 133 / 298, 32 768 points 444 / 313 /
-// 337 / 529, 131 072 points 774 / 890 / 1225 / 1299; at 16 vectors whole against
-// half load groups 121 / 136 at 2048 points, 471 / 430 at 131 072.
+// row that each wave waits for.  Measured (us per product, 2D rank 36; a wave
+// per row / two / four): 64 vectors, 8192 points (128 leaves) 204 / 151 / 144,
+// 32 768 points 306 / 292 / 331, 131 072 points 806 / 953 / 1275; 32 vectors,
+// 128 / - / 113, 194 / - / 227; 16 vectors, whole against half load groups
+// 409 / 432 at 131 072 points, 874 / 858 at 262 144.  (The LDS-staged kernel that
+// was the default before: 1299 at 131 072 points and 64 vectors.)
 struct RowForm {
   int kc, occ;
 };
 RowForm auto_form(int nvp, int64_t rows, int max_rows);
+// Composed sweep rows (FP64, at most 64 outputs): a workgroup per row and
+// 16-vector tile, the columns split over its four waves
+hipError_t launch_split_rows(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
+                             const double* data, const double* in, double* out, int nvp, int mode, int max_rows,
+                             hipStream_t s);
 // True when launch_wave_rows has a second form (occ != 0) for this pass width
 inline bool wave_alt(int nvp, bool narrow) { return nvp != 48 && !narrow; }
 // dst[R.fl_off ...] = the fragment-ordered copy of every row's matrix at src[R.data_off ...]

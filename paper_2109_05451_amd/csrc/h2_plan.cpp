@@ -150,6 +150,195 @@ void emit_rows_N(const OpLayout& L, const RowBases& B, RowsN* R) {
                       {BlockRef{0, B.yh + hoff[t], (int32_t)kr[q], 0}}});
 }
 
+namespace {
+// One basis tree: ranks per level, offsets in the matrix array of its leaf
+// bases and transfers and in the transposed array of their transposes.
+struct Basis {
+  const int64_t* k;
+  int64_t leaf, tr, leaf_t, tr_t;
+  const std::vector<int64_t>* base;  // per level: element offset of the level's first transfer
+  const Parsed* P;
+  // offset of the transfer of node c on level l
+  int64_t at(int64_t c, int64_t l) const { return (*base)[l] + (c - P->level_ptr[l]) * k[l] * k[l - 1]; }
+};
+
+// Stages s_0 = q + 1 (the points) > s_1 > ... > s_m = lmin of one sweep:
+// stage i spans the levels s_(i+1) .. s_i - 1 and level s_i.  Chosen by
+// dynamic programming over the cost of a stage: a launch in a chain of
+// dependent ones costs about 8 us beside the dense rows (4-5 us alone plus the
+// gap), the composed matrices are read at about 4 TB/s, and a workgroup
+// streams its own row at about 20 GB/s, which bounds the longest row.  For
+// operators of a few thousand points one stage covers every level, for 2^20
+// points only the levels of up to 2^11 nodes are grouped.
+std::vector<int64_t> sweep_stages(const Parsed& P, const int64_t* k, int64_t lmin, bool up, bool group) {
+  const int64_t q = P.q;
+  const int64_t* lp = P.level_ptr;
+  const double kLaunch = 8.0, kBytesPerUs = 4e6, kRowBytesPerUs = 2e4;
+  int64_t max_leaf = 0;
+  for (int64_t t = P.leaf0; t < P.nnodes; ++t) max_leaf = std::max(max_leaf, P.hi[t] - P.lo[t]);
+  std::vector<double> best(q + 2, 0.0);
+  std::vector<int64_t> prev(q + 2, lmin);
+  if (!group) {
+    std::vector<int64_t> st;
+    for (int64_t s = q + 1; s >= lmin; --s) st.push_back(s);
+    return st;
+  }
+  for (int64_t s = lmin + 1; s <= q + 1; ++s) {
+    best[s] = 1e300;
+    // columns of one node's composed row: points, or rows of x^ of its descendants on level s
+    std::vector<int64_t> width(P.nnodes, 0);
+    if (up && s <= q)
+      for (int64_t c = lp[s]; c < lp[s + 1]; ++c) width[c] = k[s];
+    double bytes = 0.0, longest = 0.0, sumk = 0.0;
+    for (int64_t lo = s - 1; lo >= lmin; --lo) {
+      bytes += 8.0 * (s <= q ? (double)(lp[s + 1] - lp[s]) * (double)k[s] : (double)P.n) * (double)k[lo];
+      sumk += (double)k[lo];
+      if (up) {
+        for (int64_t p = lp[lo]; p < lp[lo + 1]; ++p) {
+          if (s > q) width[p] = P.hi[p] - P.lo[p];
+          else width[p] = 0;
+        }
+        if (s <= q)
+          for (int64_t c = lp[lo + 1]; c < lp[lo + 2]; ++c) width[P.parent[c]] += width[c];
+        for (int64_t p = lp[lo]; p < lp[lo + 1]; ++p) longest = std::max(longest, 8.0 * (double)(width[p] * k[lo]));
+      } else {
+        longest = 8.0 * sumk * (double)(s <= q ? k[s] : max_leaf);
+      }
+      const double c = best[lo] + kLaunch + std::max(bytes / kBytesPerUs, longest / kRowBytesPerUs);
+      if (c < best[s]) {
+        best[s] = c;
+        prev[s] = lo;
+      }
+    }
+  }
+  std::vector<int64_t> st{q + 1};
+  while (st.back() > lmin) st.push_back(prev[st.back()]);
+  return st;
+}
+}  // namespace
+
+void compose_sweeps(const OpLayout& L, const RowBases& B, bool trans_op, int64_t first, bool group, Composed* C) {
+  const Parsed& P = *L.P;
+  const int64_t q = P.q;
+  const int64_t* lp = P.level_ptr;
+  *C = Composed();
+  const Basis row{P.krow, L.oU, L.oE, L.tUT, L.tET, &P.ebase, &P}, col{P.kcol, L.oV, L.oF, L.tVT, L.tFT, &P.fbase, &P};
+  const Basis &bu = trans_op ? row : col, &bd = trans_op ? col : row;
+  const int64_t lmin = std::min(first_coupling_level(P), q);
+  int64_t ext = first;
+  auto msz = [&](int64_t c) { return (int32_t)(P.hi[c] - P.lo[c]); };
+  auto task = [&](size_t depth, const ComposeTask& t) {
+    if (C->steps.size() <= depth) C->steps.resize(depth + 1);
+    if (t.m > 0 && t.n > 0) C->steps[depth].push_back(t);
+  };
+  const std::vector<int64_t> su = sweep_stages(P, bu.k, lmin, true, group),
+                             sd = sweep_stages(P, bd.k, lmin, false, group);
+  // ---- upsweep, from the points towards the root
+  for (size_t i = 0; i + 1 < su.size(); ++i) {
+    const int64_t s = su[i], lo = su[i + 1], top = s - 1;
+    C->up.emplace_back();
+    C->up_split.push_back(lo < top);
+    std::vector<RowSpec>& rows = C->up.back();
+    const bool pts = s > q;
+    const int64_t c0 = pts ? lp[q] : lp[s], c1 = pts ? lp[q + 1] : lp[s + 1];
+    // rows of the level just below the source: the stored transposes
+    for (int64_t p = lp[top]; p < lp[top + 1]; ++p) {
+      if (pts) {
+        rows.push_back({B.trans + bu.leaf_t + P.lo[p] * bu.k[q], B.xh + L.hoff[p], B.ld_h, B.ld_x, (int32_t)bu.k[q],
+                        {BlockRef{0, B.xt + P.lo[p], msz(p), 0}}});
+      } else {
+        RowSpec r{B.trans + bu.tr_t + bu.at(L.cbeg[p], s), B.xh + L.hoff[p], B.ld_h, B.ld_h, (int32_t)bu.k[top], {}};
+        for (int64_t c = L.cbeg[p]; c < L.cbeg[p + 1]; ++c)
+          r.blks.push_back({0, B.xh + L.hoff[c], (int32_t)bu.k[s], 0});
+        rows.push_back(std::move(r));
+      }
+    }
+    // the levels above: transposes of G[c][l] = G[c][l + 1] F_(ancestor of c on level l + 1)
+    std::vector<int64_t> anc(c1 - c0), g(c1 - c0);  // ancestor on level l + 1; G[c][l + 1] (matrix array, then scratch)
+    for (int64_t c = c0; c < c1; ++c) {
+      anc[c - c0] = pts ? c : P.parent[c];
+      g[c - c0] = pts ? bu.leaf + P.lo[c] * bu.k[q] : bu.tr + bu.at(c, s);
+    }
+    for (int64_t l = top - 1; l >= lo; --l) {
+      int64_t at = ext;  // rows of level l, node by node, their descendants' blocks in order
+      int64_t c = c0;
+      for (int64_t p = lp[l]; p < lp[l + 1]; ++p) {
+        RowSpec r{B.trans + at, B.xh + L.hoff[p], B.ld_h, pts ? B.ld_x : B.ld_h, (int32_t)bu.k[l], {}};
+        if (pts) r.blks.push_back({0, B.xt + P.lo[p], msz(p), 0});
+        for (; c < c1; ++c) {
+          const int64_t a = anc[c - c0];  // on level l + 1
+          if (P.parent[a] != p) break;
+          const int32_t m = pts ? msz(c) : (int32_t)bu.k[s];
+          const int64_t d = C->nscratch;
+          C->nscratch += (int64_t)m * bu.k[l];
+          task((size_t)(top - 1 - l), {g[c - c0], bu.tr + bu.at(a, l + 1), d, m, (int32_t)bu.k[l + 1], (int32_t)bu.k[l],
+                                       (l == top - 1 ? 0 : 2) | 4});
+          if (m > 0) C->trans.push_back({d, at, m, (int32_t)bu.k[l]});
+          at += (int64_t)m * bu.k[l];
+          if (!pts) {
+            // consecutive descendants are consecutive rows of x^ where the level's tree rows are all used
+            const int64_t in = B.xh + L.hoff[c];
+            if (!r.blks.empty() && r.blks.back().in_off + r.blks.back().width == in) r.blks.back().width += m;
+            else r.blks.push_back({0, in, m, 0});
+          }
+          g[c - c0] = d;
+          anc[c - c0] = p;
+        }
+        rows.push_back(std::move(r));
+      }
+      ext = at;
+    }
+  }
+  // ---- downsweep, from the root towards the points
+  for (size_t i = sd.size() - 1; i-- > 0;) {
+    const int64_t s = sd[i], lo = sd[i + 1], top = s - 1;
+    const bool pts = s > q, split = lo < top;
+    std::vector<RowSpec> rows;
+    const int64_t c0 = pts ? lp[q] : lp[s], c1 = pts ? lp[q + 1] : lp[s + 1];
+    for (int64_t c = c0; c < c1; ++c) {
+      const int32_t m = pts ? msz(c) : (int32_t)bd.k[s];
+      const int64_t stored = pts ? bd.leaf + P.lo[c] * bd.k[q] : bd.tr + bd.at(c, s);
+      RowSpec r{split ? B.trans + ext : B.mat + stored, pts ? B.zn + P.lo[c] : B.yh + L.hoff[c], pts ? B.ld_x : B.ld_h,
+                B.ld_h, m, {}};
+      int64_t a = pts ? c : P.parent[c];  // ancestor on level l
+      int64_t prev = stored;
+      for (int64_t l = top; l >= lo; --l) {
+        r.blks.push_back({0, B.yh + L.hoff[a], (int32_t)bd.k[l], 0});
+        if (split) {
+          if (l == top) {
+            task(0, {stored, 0, ext, m, 0, (int32_t)bd.k[l], 0});
+          } else {
+            // a is the ancestor on level l; the transfer used is its child's on the path
+            int64_t ch = pts ? c : P.parent[c];
+            for (int64_t x = top; x > l + 1; --x) ch = P.parent[ch];
+            task((size_t)(top - l), {prev, bd.tr + bd.at(ch, l + 1), ext, m, (int32_t)bd.k[l + 1], (int32_t)bd.k[l], 1});
+          }
+          prev = ext;
+          ext += (int64_t)m * bd.k[l];
+        }
+        if (l > lo) a = P.parent[a];
+      }
+      rows.push_back(std::move(r));
+    }
+    if (pts) {
+      C->out = std::move(rows);
+      C->out_split = split;
+    } else {
+      C->down.push_back(std::move(rows));
+      C->down_split.push_back(split);
+    }
+  }
+  C->ntrans = (ext + 31) / 32 * 32;
+}
+
+bool composed_fits(const Composed& C) {
+  for (const auto* v : {&C.up, &C.down})
+    for (const auto& rows : *v)
+      for (const RowSpec& r : rows)
+        if ((int64_t)r.blks.size() > kNbMax) return false;
+  return true;
+}
+
 void append_row(RowTables& t, const RowSpec& r) {
   RowDesc R{};
   R.data_off = r.data_off;

@@ -297,8 +297,6 @@ hipError_t launch_tree(const int2* ranges, int64_t nwg, const TreeLevels& L, con
 #undef H2_TREE
   return hipGetLastError();
 }
-template hipError_t launch_tree<double>(const int2*, int64_t, const TreeLevels&, const RowDesc*, const int32_t*,
-                                        const int64_t*, const double*, double* const[4], int, int, hipStream_t);
 template hipError_t launch_tree<float>(const int2*, int64_t, const TreeLevels&, const RowDesc*, const int32_t*,
                                        const int64_t*, const float*, double* const[4], int, int, hipStream_t);
 

@@ -68,7 +68,11 @@ constexpr int kChunk = 1024;  // columns of one source-row table (4 KB of LDS pe
 // count past the next group's loads.  In launches of mixed rows the loads of a
 // row's empty tiles are skipped (cheaper than loading them, though the waits
 // then count the fewer).
-template <typename T, int NT, int NTW, int NF, int TQ, int U, int W, bool FL, bool WHOLE>
+// KS: a workgroup per row and vector range, the row's columns in four equal
+// pieces, one per wave, the partial sums added through LDS in wave order: the
+// composed sweep rows, few and long, where one wave's chain of loads is what
+// the launch waits for.
+template <typename T, int NT, int NTW, int NF, int TQ, int U, int W, bool FL, bool WHOLE, bool KS = false>
 __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__ rows, int64_t nrows,
                                                      const int32_t* __restrict__ colend,
                                                      const int64_t* __restrict__ in_off,
@@ -77,19 +81,21 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
   typedef typename Mfma<T>::acc CT;
   typedef T t2 __attribute__((ext_vector_type(2), aligned(sizeof(T))));  // any element offset
   typedef double v2 __attribute__((ext_vector_type(2)));
-  constexpr int NVP = 16 * NT, WPR = NT / NTW, RPW = 4 / WPR;
+  constexpr int NVP = 16 * NT, WPR = NT / NTW, RPW = KS ? 1 : 4 / WPR;
   constexpr int G = 4 * U;           // columns per load group
   constexpr int NA = NF + TQ;        // A values per step
   constexpr bool BV = NTW % 2 == 0;  // tiles j: vectors NTW * arow + j, else 16 j + arow
   constexpr int ES = sizeof(T);
   typedef const __attribute__((address_space(1))) char* gptr;
   static_assert((U == 2 || U % 4 == 0) && kChunk % G == 0, "load groups");
+  constexpr int LDP = 16 * NTW;  // LDS row of the partial sums
+  __shared__ __align__(16) double part[KS ? 4 * (16 * NF + 4 * TQ) * LDP : 1];
   // source rows of a chunk's columns; a lane's U steps of a group adjacent,
   // and two groups of padding for the reads ahead
   __shared__ __align__(16) uint32_t s_src[4][kChunk + 2 * G];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int slot = wave / WPR, vt0 = (wave % WPR) * NTW;
+  const int slot = KS ? 0 : wave / WPR, vt0 = KS ? (int)(blockIdx.x % WPR) * NTW : (wave % WPR) * NTW;
   const int arow = lane & 15, akk = lane >> 4;
   const int vcol = 16 * vt0 + (BV ? NTW * arow : arow);  // first vector of the lane
   uint32_t* src = s_src[wave];
@@ -100,15 +106,18 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
   // the row order and their shared input segments meet in that XCD's L2
   const int64_t per = remap ? (nrows + 7) / 8 : nrows;
   const int64_t base = remap ? (int64_t)(blockIdx.x % 8) * per : 0;
-  const int64_t wg = remap ? blockIdx.x / 8 : blockIdx.x;
+  const int64_t wg = KS ? blockIdx.x / WPR : remap ? blockIdx.x / 8 : blockIdx.x;
   const int64_t nwg = remap ? gridDim.x / 8 : gridDim.x;
-  for (int64_t jr = wg * RPW + slot; jr < per; jr += nwg * RPW) {
+  for (int64_t jr = KS ? wg : wg * RPW + slot; jr < per; jr += KS ? nrows : nwg * RPW) {
     const int64_t ri = base + jr;
     if (ri >= nrows) break;
     const RowDesc R = rows[ri];
     const int m = R.nrows;
     if (m <= 0) continue;
-    const int ncols = R.blk_end > R.blk_begin ? colend[R.blk_end - 1] : 0;
+    const int allcols = R.blk_end > R.blk_begin ? colend[R.blk_end - 1] : 0;
+    const int piece = KS ? ((allcols + 3) / 4 + G - 1) / G * G : 0;  // columns per wave
+    const int cbeg = KS ? min(wave * piece, allcols) : 0;
+    const int ncols = KS ? min(cbeg + piece, allcols) : allcols;
     CT acc[NF][NTW];
     T acc4[TQ > 0 ? TQ : 1][NTW];
 #pragma unroll
@@ -138,7 +147,7 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
 #pragma unroll
       for (int t = 0; t < TQ; ++t) voff[NF + t] = (akk * m + 16 * NF + (TQ == 1 ? arow & 3 : 2 * (arow & 3) + t)) * ES;
     }
-    gptr sbase = (gptr)(data + (FL ? R.fl_off : R.data_off));
+    gptr sbase = (gptr)(data + (FL ? R.fl_off : R.data_off) + (int64_t)m * cbeg);
     const int64_t sstep = (int64_t)4 * m * ES;  // bytes of one step
 
     T a[U][NA], a2[U][NA];
@@ -229,7 +238,7 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
     };
 
     int bcur = R.blk_begin, bstart = 0;  // block of the chunk's first column and its first column
-    for (int c0 = 0; c0 < ncols; c0 += kChunk) {
+    for (int c0 = cbeg; c0 < ncols; c0 += kChunk) {
       const int cn = min(kChunk, ncols - c0);
       // source row of each column of the chunk: 64 blocks' table entries
       // loaded by the lanes, then one block at a time written by the wave
@@ -316,19 +325,19 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
     // stores: vectors vcol + j (NTW even) or vcol + 16 j of the tile's rows
     auto put = [&](int row, auto val) __attribute__((always_inline)) {
       if (row >= m) return;
-      double* o = out + (R.out_off + row) * NVP + vcol;
+      double* o = KS ? part + (wave * m + row) * LDP + vcol - 16 * vt0 : out + (R.out_off + row) * NVP + vcol;
       if constexpr (BV) {
 #pragma unroll
         for (int j = 0; j < NTW; j += 2) {
           v2 v = {val(j), val(j + 1)};
           v2* p = reinterpret_cast<v2*>(o + j);
-          if (mode != MODE_STORE) v += *p;
+          if (!KS && mode != MODE_STORE) v += *p;
           *p = v;
         }
       } else {
 #pragma unroll
         for (int j = 0; j < NTW; ++j) {
-          if (mode == MODE_STORE) o[16 * j] = val(j);
+          if (KS || mode == MODE_STORE) o[16 * j] = val(j);
           else o[16 * j] += val(j);
         }
       }
@@ -345,6 +354,17 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
 #pragma unroll
       for (int t = 0; t < TQ; ++t)
         put(16 * NF + (FL || TQ == 1 ? 4 * t + akk : 2 * akk + t), [&](int j) { return acc4[t][j]; });
+    }
+    if constexpr (KS) {
+      __syncthreads();
+      for (int e = threadIdx.x; e < m * LDP; e += kT) {
+        const int row = e / LDP, v = e % LDP;
+        double sum = part[row * LDP + v];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) sum += part[(w * m + row) * LDP + v];
+        double* o = out + (R.out_off + row) * NVP + 16 * vt0 + v;
+        *o = mode == MODE_STORE ? sum : *o + sum;
+      }
     }
   }
 }
@@ -626,6 +646,41 @@ void launch_rows_of(const Args<T>& A, int max_rows) {
 // the four waves of a workgroup.
 constexpr int64_t kColsSplit = 8192;
 
+struct SplitArgs {
+  const RowDesc* rows;
+  int64_t nrows;
+  const int32_t* colend;
+  const int64_t* in_off;
+  const double *data, *in;
+  double* out;
+  int mode;
+  hipStream_t s;
+};
+
+template <int NT, int NTW, int NF, int TQ, int U>
+void launch_split_form(const SplitArgs& A) {
+  constexpr int W0 = form_waves(form_regs(8, NTW, NF, TQ, U));
+  constexpr int LDS = 4 * (16 * NF + 4 * TQ) * 16 * NTW * 8 + 4 * (kChunk + 8 * U) * 4;
+  constexpr int W = W0 * LDS <= 160 * 1024 ? W0 : 2;  // workgroups per CU that the LDS holds
+  hipLaunchKernelGGL((k_wave_rows<double, NT, NTW, NF, TQ, U, W, false, false, true>),
+                     dim3((unsigned)(A.nrows * (NT / NTW))), dim3(kT), 0, A.s, A.rows, A.nrows, A.colend, A.in_off,
+                     A.data, A.in, A.out, A.mode, 0);
+}
+
+template <int NT, int NTW, int U>
+void launch_split_of(const SplitArgs& A, int max_rows) {
+  const int nf = max_rows >> 4, rem = max_rows & 15;
+  if (nf == 2 && rem >= 1 && rem <= 4) return launch_split_form<NT, NTW, 2, 1, U>(A);
+  if (nf == 3 && rem >= 1 && rem <= 4) return launch_split_form<NT, NTW, 3, 1, U>(A);
+  switch (nf + (rem > 0 ? 1 : 0)) {
+    case 0:
+    case 1: return launch_split_form<NT, NTW, 1, 0, U>(A);
+    case 2: return launch_split_form<NT, NTW, 2, 0, U>(A);
+    case 3: return launch_split_form<NT, NTW, 3, 0, U>(A);
+    default: return launch_split_form<NT, NTW, 4, 0, U>(A);
+  }
+}
+
 struct ColArgs {
   const RowDesc* rows;
   int64_t nrows;
@@ -686,12 +741,28 @@ hipError_t launch_wave_cols(const RowDesc* rows, int64_t nrows, const int64_t* b
   return hipGetLastError();
 }
 
+hipError_t launch_split_rows(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
+                             const double* data, const double* in, double* out, int nvp, int mode, int max_rows,
+                             hipStream_t s) {
+  if (nrows == 0) return hipSuccess;
+  if (max_rows > 64) return hipErrorInvalidValue;
+  const SplitArgs A{rows, nrows, colend, in_off, data, in, out, mode, s};
+  switch (nvp) {
+    case 16: launch_split_of<1, 1, 4>(A, max_rows); break;
+    case 32: launch_split_of<2, 1, 4>(A, max_rows); break;
+    case 48: launch_split_of<3, 1, 4>(A, max_rows); break;
+    case 64: launch_split_of<4, 1, 4>(A, max_rows); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 RowForm auto_form(int nvp, int64_t rows, int max_rows) {
   if (max_rows > 64) return {64, 0};
-  if (nvp == 16) return {kWaveRows, rows >= 512 ? 5 : 0};
-  if (nvp == 32) return rows >= 512 ? RowForm{kWaveRows, 5} : RowForm{kWaveTiles, 0};
-  if (nvp == 48 || rows >= 1024) return {kWaveRows, 0};
-  return rows >= 192 ? RowForm{kWaveRows, 5} : RowForm{kWaveTiles, 0};
+  if (nvp == 16) return {kWaveRows, rows >= 8192 ? 5 : 0};
+  if (nvp == 48) return {kWaveRows, 0};
+  if (rows < 400) return {kWaveTiles, 0};
+  return {kWaveRows, nvp == 64 && rows < 1200 ? 5 : 0};
 }
 
 template <typename T>
