@@ -55,6 +55,7 @@ void append_gather(GatherTables& t, const RowSpec& r) {
     t.data.push_back(b.data);
     t.in_off.push_back(b.in_off);
     t.mr.push_back(b.mr);
+    R.pad = std::max(R.pad, b.mr);
   }
   R.blk_end = (int32_t)t.data.size();
   R.out_ld = r.out_ld;
@@ -122,9 +123,16 @@ void add_stream_phase(h2_op_s* h, const std::vector<RowSpec>& rows, int arr, int
   add_stream_rows(h, rows, o.data(), o.size(), arr, in, out, mode, dst);
 }
 
-// Rows first, first + step, ... of `rows` as one launch of the transposed kernel.
+// Rows order[first], order[first + step], ... of `rows` (longest first) as one
+// launch of the transposed kernels.
 void add_gather_phase(h2_op_s* h, const std::vector<RowSpec>& rows, int in, int out, std::vector<Launch>& dst,
                       size_t first = 0, size_t step = 1) {
+  std::vector<int64_t> w(rows.size(), 0);
+  std::vector<size_t> o(rows.size());
+  std::iota(o.begin(), o.end(), 0);
+  for (size_t i = 0; i < rows.size(); ++i)
+    for (const BlockRef& b : rows[i].blks) w[i] += (int64_t)b.mr * rows[i].nrows;
+  std::stable_sort(o.begin(), o.end(), [&](size_t a, size_t b) { return w[a] > w[b]; });
   Launch L;
   L.kind = KIND_GATHER;
   L.arr = ARR_MAT;
@@ -132,10 +140,16 @@ void add_gather_phase(h2_op_s* h, const std::vector<RowSpec>& rows, int in, int 
   L.out = out;
   L.mode = MODE_STORE;
   L.row_begin = (int64_t)h->gt.rows.size();
+  bool fits = true;
   for (size_t i = first; i < rows.size(); i += step) {
-    append_gather(h->gt, rows[i]);
-    L.max_rows = std::max(L.max_rows, rows[i].nrows);
+    append_gather(h->gt, rows[o[i]]);
+    const RowDesc& R = h->gt.rows.back();
+    L.max_rows = std::max(L.max_rows, R.nrows);
+    const int sl = cols_slots(R.nrows, R.pad);
+    fits = fits && sl > 0;
+    L.slots = std::max(L.slots, sl);
   }
+  if (!fits) L.slots = 0;
   L.row_count = (int64_t)h->gt.rows.size() - L.row_begin;
   if (L.row_count) dst.push_back(L);
 }
@@ -771,6 +785,9 @@ int run_launch(h2_op_s* h, const Workspace& w, const Launch& L, int nv, const Ep
   } else if (L.kind == KIND_WIDE) {
     e = launch_rows_wide(h->wide.d_rows + L.row_begin, L.row_count, h->wide.d_colend, h->wide.d_in_off, data,
                          bufs[L.in], out, nv, s);
+  } else if (!lowp && L.slots > 0) {
+    e = launch_cols(h->gt.d_rows + L.row_begin, L.row_count, h->gt.d_data, h->gt.d_mr, h->gt.d_in_off, data,
+                    bufs[L.in], out, nv, L.slots, s, L.lowrank ? 0 : h->dense_stream_grid);
   } else {
     e = lowp ? launch_gather<float>(h->gt.d_rows + L.row_begin, L.row_count, h->gt.d_data, h->gt.d_mr,
                                     h->gt.d_in_off, data32, bufs[L.in], out, nv, s)
@@ -1010,6 +1027,7 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
       L.max_rows = std::max(L.max_rows, dense2[0].max_rows);
       L.min_rows = std::min(L.min_rows, dense2[0].min_rows);
       L.max_cols = std::max(L.max_cols, dense2[0].max_cols);
+      L.slots = L.slots && dense2[0].slots ? std::max(L.slots, dense2[0].slots) : 0;
       STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));
     } else
       for (const Launch& L : dense1) STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));

@@ -71,7 +71,7 @@ struct RowDesc {
   int32_t nrows;     // output length
   int32_t blk_begin; // blocks [blk_begin, blk_end) in the per-block tables
   int32_t blk_end;
-  int32_t pad;
+  int32_t pad;       // transposed rows: largest block height
   int64_t out_ld;    // output stride between vectors
   int64_t in_ld;     // input stride between vectors
   int64_t fl_off;    // element offset of the row's fragment-ordered copy (wave-row kernels), even
@@ -115,6 +115,7 @@ struct Launch {
   int64_t row_begin = 0, row_count = 0;  // slice of the kind's row table
   int32_t max_rows = 0;                   // largest output length of its rows
   int64_t max_cols = 0;                   // most input columns of its rows
+  int slots = 0;                          // transposed rows: form of the streaming kernel (cols_slots)
   int32_t min_rows = kMaxDim;             // smallest output length of its rows that is not zero
   bool split = false;                     // composed sweep rows of several levels (launch_split_rows on the MFMA path)
   bool lowrank = true;                    // false for the dense near-field phase (always FP64)
@@ -551,6 +552,12 @@ hipError_t launch_permute_out_rm2(const double* Z, const double* Z2, const int32
                                   double* Y, int64_t ldy, int64_t n, int nv, int nvp, hipStream_t s);
 hipError_t launch_rows_wide(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
                             const double* data, const double* in, double* out, int nv, hipStream_t s);
+// op 'T' rows, FP64 and at most kPassVectors vectors, streamed; `slots` from
+// cols_slots (0: no form); grid 0 = a workgroup per row
+int cols_slots(int max_rows, int max_mr);
+hipError_t launch_cols(const RowDesc* rows, int64_t nrows, const int64_t* bdata, const int32_t* bmr,
+                       const int64_t* bin, const double* data, const double* in, double* out, int nv, int slots,
+                       hipStream_t s, int64_t grid);
 template <typename T>
 hipError_t launch_gather(const RowDesc* rows, int64_t nrows, const int64_t* bdata, const int32_t* bmr,
                          const int64_t* bin, const T* data, const double* in, double* out, int nv,
