@@ -215,7 +215,10 @@ def measured_copy_gbs(torch, nbytes: int = 4 << 30, reps: int = 5) -> float:
 def launches_per_product(g) -> int:
     """Kernel launches of one single-vector product: the plan's upsweep,
     coupling, downsweep and dense launches, the leaf expansion and the input
-    permutation."""
+    permutation; a small operator's dense rows, upsweep and permutation are one
+    launch ("input")."""
+    if any(line.startswith("input ") for line in g.plan_info().splitlines()):
+        return 2 + sum(1 for line in g.plan_info().splitlines() if line.startswith("couple "))
     names = ("up ", "couple ", "down ", "dense1 ", "dense2 ", "out ")
     return 1 + sum(1 for line in g.plan_info().splitlines() if line.startswith(names) and "skipped" not in line)
 

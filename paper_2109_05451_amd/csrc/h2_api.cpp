@@ -343,6 +343,7 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
   auto msz = [&](int64_t c) { return (int32_t)(P.hi[c] - P.lo[c]); };
 
   // ---- plan for op 'N': rows from the shared emitter (column-major layout)
+  std::vector<RowSpec> dense_rows;
   {
     RowsN R;
     RowBases B;
@@ -416,6 +417,7 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
       return H2_EUNSUPPORTED;
     }
     plan.out = outl[0];
+    dense_rows = std::move(R.dense);
   }
   // ---- composed sweeps of both ops (a shared basis serves both with the same
   // rows); their matrices follow the transposed bases
@@ -434,6 +436,20 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
     if ((rc = add_composed(h, cn, h->planN)) || (rc = add_composed(h, h->shared ? cn : ct, h->planT))) return rc;
   }
   const int64_t ntrans_all = h->shared ? cn.ntrans : ct.ntrans;
+  {
+    // one stage each way: the input's readers as one launch
+    Plan& plan = h->planN;
+    auto narrow = [](const std::vector<Launch>& v) { return v.size() == 1 && v[0].kind == KIND_STREAM; };
+    if (narrow(plan.upc) && plan.downc.empty() && narrow(plan.dense) && narrow(plan.dense2) && narrow(plan.couple)) {
+      std::vector<Launch> v;
+      const std::vector<size_t> od = order_by_work(dense_rows), ou = order_by_work(cn.up[0]);
+      add_stream_rows(h, dense_rows, od.data(), od.size(), ARR_MAT, BUF_XT, BUF_ZN, MODE_STORE, v);
+      add_stream_rows(h, cn.up[0], ou.data(), ou.size(), ARR_TRANS, BUF_XT, BUF_XH, MODE_STORE, v);
+      plan.first = v[0];
+      plan.first.row_count += v[1].row_count;
+      plan.first_dense = v[0].row_count;
+    }
+  }
   std::vector<int2> tree_ranges;
   h->tree_ok = build_tree_groups(h, P, lay, &tree_ranges);
   if (!h->tree_ok) {
@@ -994,6 +1010,16 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
   Epilogue ep{w.zn, h->d_perm, alpha, beta, Y, ldy, h->n};
   int rc;
 #define STEP(x) do { if ((rc = (x)) != H2_OK) return rc; } while (0)
+  // small operators on the streaming path: three launches in a row, no side
+  // stream (the general sequence when its phases are to be timed)
+  if (nvp == 0 && comp && !trans && !ev && plan.first.row_count > 0) {
+    const FirstArgs F{h->d_perm, ldx, plan.first_dense, h->d_trans, w.xh};
+    HIP_TRY(launch_rows_first(h->rt.d_rows + plan.first.row_begin, plan.first.row_count, h->rt.d_colend,
+                              h->rt.d_in_off, h->d_mat, X, w.zn, nv, F, s),
+            "kernel launch");
+    for (const Launch& L : plan.couple) STEP(run_launch(h, w, L, nv, ep, s));
+    return run_launch(h, w, plan.outc, nv, ep, s);
+  }
   STEP(mark(0, s));
   if (nvp) HIP_TRY(launch_permute_in_rm(X, ldx, h->d_pinv, w.xt, h->n, nv, nvp, s), "permute");
   else HIP_TRY(launch_permute_in(X, ldx, h->d_perm, w.xt, h->n, nv, s), "permute");
@@ -1017,10 +1043,16 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
   // product's views, takes schedule 2's order instead)
   const bool split = sched == 3 && !fused && !x32 && !down.empty() && !plan.couple_deep.empty() && !up.empty() &&
                      w.side2 && w.ev_deep && w.ev_deep_done;
+  // op 'T' of a small operator, one stage each way: its few launches all on the
+  // caller's stream (the events of a side stream cost more than it overlaps)
+  const bool inl = trans && nvp == 0 && comp && up.size() == 1 && down.empty();
+  hipStream_t side = inl ? s : w.side;
   auto fork_dense1 = [&]() -> int {
-    HIP_TRY(hipEventRecord(w.ev_fork, s), "hipEventRecord(fork)");
-    HIP_TRY(hipStreamWaitEvent(w.side, w.ev_fork, 0), "hipStreamWaitEvent(fork)");
-    STEP(mark(5, w.side));
+    if (!inl) {
+      HIP_TRY(hipEventRecord(w.ev_fork, s), "hipEventRecord(fork)");
+      HIP_TRY(hipStreamWaitEvent(side, w.ev_fork, 0), "hipStreamWaitEvent(fork)");
+    }
+    STEP(mark(5, side));
     if (whole) {
       Launch L = dense1[0];
       L.row_count += dense2[0].row_count;
@@ -1028,10 +1060,10 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
       L.min_rows = std::min(L.min_rows, dense2[0].min_rows);
       L.max_cols = std::max(L.max_cols, dense2[0].max_cols);
       L.slots = L.slots && dense2[0].slots ? std::max(L.slots, dense2[0].slots) : 0;
-      STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));
+      STEP(run_launch(h, w, L, nv, ep, side, nvp, -1, prec));
     } else
-      for (const Launch& L : dense1) STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));
-    STEP(mark(9, w.side));
+      for (const Launch& L : dense1) STEP(run_launch(h, w, L, nv, ep, side, nvp, -1, prec));
+    STEP(mark(9, side));
     return H2_OK;
   };
   if (sched != 1) STEP(fork_dense1());
@@ -1060,15 +1092,15 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
     STEP(mark(12, s));
   }
   // second half of the dense rows, beside the downsweep and the leaf expansion
-  if (sched != 2 && sched != 3) {
+  if (sched != 2 && sched != 3 && !inl) {
     HIP_TRY(hipEventRecord(w.ev_mid, s), "hipEventRecord(mid)");
     HIP_TRY(hipStreamWaitEvent(w.side, w.ev_mid, 0), "hipStreamWaitEvent(mid)");
   }
-  STEP(mark(10, w.side));
+  STEP(mark(10, side));
   if (!whole)
-    for (const Launch& L : dense2) STEP(run_launch(h, w, L, nv, ep, w.side, nvp, -1, prec));
-  STEP(mark(6, w.side));
-  HIP_TRY(hipEventRecord(w.ev_join, w.side), "hipEventRecord(join)");
+    for (const Launch& L : dense2) STEP(run_launch(h, w, L, nv, ep, side, nvp, -1, prec));
+  STEP(mark(6, side));
+  if (!inl) HIP_TRY(hipEventRecord(w.ev_join, w.side), "hipEventRecord(join)");
   // Multi-vector path: the leaf expansion U y^ goes to its own buffer w.zx,
   // beside the dense rows (the fused downsweep ends with it); the output
   // permutation adds the dense partial, the same Z + U y^ addition.
@@ -1084,7 +1116,7 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
   }
   if (zx && !fused) STEP(run_launch(h, w, outl, nv, ep, s, nvp, MODE_STORE, prec, false, w.zx));
   STEP(mark(4, s));
-  HIP_TRY(hipStreamWaitEvent(s, w.ev_join, 0), "hipStreamWaitEvent(join)");
+  if (!inl) HIP_TRY(hipStreamWaitEvent(s, w.ev_join, 0), "hipStreamWaitEvent(join)");
   STEP(mark(7, s));
   if (zx) {
     // Y = alpha (Z + U y^)[pinv] + beta Y
@@ -1782,6 +1814,7 @@ int h2_plan_info(h2_handle h, char* buf, size_t cap, size_t* needed) {
       t += line;
     }
   const Plan& P = h->planN;
+  if (P.first.row_count > 0) dump("input", std::vector<Launch>{P.first});
   dump("up", P.upc);
   dump("couple", P.couple);
   dump("couple_deep", P.couple_deep);

@@ -153,6 +153,10 @@ struct Plan {
   // the sweeps in composed stages (FP64)
   std::vector<Launch> upc, downc;
   Launch outc;
+  // where one stage covers each sweep (op 'N'): the dense rows, then the
+  // upsweep stage's, as one launch of the streaming path; no rows otherwise
+  Launch first;
+  int64_t first_dense = 0;
 };
 
 // Fused sweeps of the multi-vector path (h2_tree_kernels.hip): the levels
@@ -205,6 +209,15 @@ struct Epilogue {
   double* Y;
   int64_t ldy;
   int64_t n;
+};
+
+// A small operator's first launch (launch_rows_first).
+struct FirstArgs {
+  const int32_t* perm;  // tree position -> original index
+  int64_t ldx;          // the caller's X
+  int64_t ndense;       // dense rows before the upsweep rows
+  const double* data2;  // upsweep rows: matrix data and x^
+  double* out2;
 };
 
 struct LevelInfo {
@@ -456,6 +469,9 @@ template <typename T>
 hipError_t launch_rows(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
                        const T* data, const double* in, double* out, int nv, int mode, const Epilogue& ep,
                        hipStream_t s, int64_t grid = 0);
+hipError_t launch_rows_first(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
+                             const double* data, const double* X, double* out, int nv, const FirstArgs& F,
+                             hipStream_t s);
 template <typename T>
 hipError_t launch_rows_mfma(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
                             const T* data, const double* in, double* out, int nvp, int mode, int max_rows,
