@@ -36,15 +36,40 @@ int hip_fail(hipError_t e, const char* what) {
     if (e_ != hipSuccess) return hip_fail(e_, what); \
   } while (0)
 
-template <class T>
-int upload(const std::vector<T>& v, T** dst, int64_t* bytes) {
-  *dst = nullptr;
-  if (v.empty()) return H2_OK;
-  HIP_TRY(hipMalloc(reinterpret_cast<void**>(dst), v.size() * sizeof(T)), "hipMalloc(index)");
-  HIP_TRY(hipMemcpy(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice), "hipMemcpy(index)");
-  *bytes += (int64_t)(v.size() * sizeof(T));
-  return H2_OK;
-}
+// Device arrays of one allocation: `add` every array, then `commit`.
+class Uploads {
+ public:
+  template <class T>
+  void add(const std::vector<T>& v, T** dst) {
+    *dst = nullptr;
+    if (v.empty()) return;
+    items_.push_back({v.data(), v.size() * sizeof(T), reinterpret_cast<void**>(dst), total_});
+    total_ = (total_ + v.size() * sizeof(T) + 255) / 256 * 256;
+    bytes_ += (int64_t)(v.size() * sizeof(T));
+  }
+  int commit(void** base) {
+    *base = nullptr;
+    if (total_ == 0) return H2_OK;
+    HIP_TRY(hipMalloc(base, total_), "hipMalloc(index)");
+    for (const Item& it : items_) {
+      *it.dst = static_cast<char*>(*base) + it.at;
+      HIP_TRY(hipMemcpy(*it.dst, it.src, it.bytes, hipMemcpyHostToDevice), "hipMemcpy(index)");
+    }
+    return H2_OK;
+  }
+  int64_t bytes() const { return bytes_; }
+
+ private:
+  struct Item {
+    const void* src;
+    size_t bytes;
+    void** dst;
+    size_t at;
+  };
+  std::vector<Item> items_;
+  size_t total_ = 0;
+  int64_t bytes_ = 0;
+};
 
 void append_gather(GatherTables& t, const RowSpec& r) {
   RowDesc R{};
@@ -165,11 +190,8 @@ void drop_graphs(h2_op_s* h) {
 void free_device(h2_op_s* h) {
   drop_graphs(h);
   auto F = [](void* p) { if (p) (void)hipFree(p); };
-  F(h->d_mat); F(h->d_trans); F(h->d_perm); F(h->d_pinv); F(h->d_mat32); F(h->d_trans32);
+  F(h->d_base); F(h->d_index); F(h->d_mat32); F(h->d_trans32);
   F(h->d_mat16); F(h->d_trans16); F(h->d_fl); F(h->d_fl32);
-  F(h->rt.d_rows); F(h->rt.d_colend); F(h->rt.d_in_off);
-  F(h->wide.d_rows); F(h->wide.d_colend); F(h->wide.d_in_off);
-  F(h->gt.d_rows); F(h->gt.d_data); F(h->gt.d_mr); F(h->gt.d_in_off); F(h->d_tree_ranges);
   for (auto& set : h->ev_pool)
     for (hipEvent_t e : set)
       if (e) (void)hipEventDestroy(e);
@@ -575,8 +597,12 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
 
   // ---- upload
   const int64_t mat_bytes = P.off_end - P.off_U;
+  const int64_t mat_alloc = mat_bytes > 0 ? (mat_bytes + kRowSlack + 255) / 256 * 256 : 0;
+  const int64_t trans_alloc = ntrans_all > 0 ? ntrans_all * (int64_t)sizeof(double) + kRowSlack : 0;
+  if (mat_alloc + trans_alloc > 0)
+    HIP_TRY(hipMalloc(&h->d_base, mat_alloc + trans_alloc), "hipMalloc(matrix data)");
   if (mat_bytes > 0) {
-    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&h->d_mat), mat_bytes + kRowSlack), "hipMalloc(matrix data)");
+    h->d_mat = static_cast<double*>(h->d_base);
     const int64_t host_bytes = d_dense ? P.off_D - P.off_U : mat_bytes;
     if (host_bytes > 0)
       HIP_TRY(hipMemcpy(h->d_mat, buf + P.off_U, host_bytes, hipMemcpyHostToDevice), "hipMemcpy(matrix data)");
@@ -590,8 +616,7 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
   if (ntrans_all > 0) {
     std::vector<TransTask> tasks;
     transpose_tasks(lay, &tasks);
-    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&h->d_trans), ntrans_all * sizeof(double) + kRowSlack),
-            "hipMalloc(trans)");
+    h->d_trans = reinterpret_cast<double*>(static_cast<char*>(h->d_base) + mat_alloc);
     HIP_TRY(hipMemset(h->d_trans, 0, ntrans_all * sizeof(double)), "hipMemset(trans)");
     if (!tasks.empty()) {
       TransTask* d_tasks = nullptr;
@@ -602,8 +627,8 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
       (void)hipFree(d_tasks);
       if (e != hipSuccess) return hip_fail(e, "transposed basis copies");
     }
-    int rc;
-    if ((rc = run_compose(cn, h->d_mat, h->d_trans)) || (rc = run_compose(ct, h->d_mat, h->d_trans))) return rc;
+    const int rc = run_compose({&cn, &ct}, P, h->d_mat, h->d_trans);
+    if (rc != H2_OK) return rc;
   }
   h->prefix.assign((size_t)(P.off_U + 7) / 8, 0);
   std::memcpy(h->prefix.data(), buf, (size_t)P.off_U);
@@ -630,16 +655,23 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
   for (int& f : h->planT.out.flp) f = 0;
   for (int& f : h->planT.outc.flp) f = 0;
   if (h->planT.out.kind != KIND_STREAM) h->mfma_t_ok = false;
-  int64_t ib = 0;
-  int rc;
-  if ((rc = upload(perm, &h->d_perm, &ib)) || (rc = upload(pinv, &h->d_pinv, &ib)) || (rc = upload(h->rt.rows, &h->rt.d_rows, &ib)) ||
-      (rc = upload(h->rt.colend, &h->rt.d_colend, &ib)) || (rc = upload(h->rt.in_off, &h->rt.d_in_off, &ib)) ||
-      (rc = upload(h->wide.rows, &h->wide.d_rows, &ib)) ||
-      (rc = upload(h->wide.colend, &h->wide.d_colend, &ib)) ||
-      (rc = upload(h->wide.in_off, &h->wide.d_in_off, &ib)) || (rc = upload(h->gt.rows, &h->gt.d_rows, &ib)) ||
-      (rc = upload(h->gt.data, &h->gt.d_data, &ib)) || (rc = upload(h->gt.mr, &h->gt.d_mr, &ib)) ||
-      (rc = upload(h->gt.in_off, &h->gt.d_in_off, &ib)) || (rc = upload(tree_ranges, &h->d_tree_ranges, &ib)))
-    return rc;
+  Uploads up;
+  up.add(perm, &h->d_perm);
+  up.add(pinv, &h->d_pinv);
+  up.add(h->rt.rows, &h->rt.d_rows);
+  up.add(h->rt.colend, &h->rt.d_colend);
+  up.add(h->rt.in_off, &h->rt.d_in_off);
+  up.add(h->wide.rows, &h->wide.d_rows);
+  up.add(h->wide.colend, &h->wide.d_colend);
+  up.add(h->wide.in_off, &h->wide.d_in_off);
+  up.add(h->gt.rows, &h->gt.d_rows);
+  up.add(h->gt.data, &h->gt.d_data);
+  up.add(h->gt.mr, &h->gt.d_mr);
+  up.add(h->gt.in_off, &h->gt.d_in_off);
+  up.add(tree_ranges, &h->d_tree_ranges);
+  const int rc = up.commit(&h->d_index);
+  if (rc != H2_OK) return rc;
+  const int64_t ib = up.bytes();
   h->index_bytes = ib;
   h->stats.device_bytes = mat_bytes + ntrans_all * (int64_t)sizeof(double) + ib;
   return H2_OK;

@@ -55,13 +55,32 @@ class Arena {
     (void)hipDeviceSynchronize();  // the uploads read host_ until they ran
     for (void* p : ptrs_) (void)hipFree(p);
   }
+  // Room for `bytes` of later allocations in one device allocation (each one
+  // and its release cost tens of microseconds); where it does not fit, they are
+  // made one by one.
+  void reserve(size_t bytes) {
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    ptrs_.push_back(p);
+    pool_ = static_cast<uint8_t*>(p);
+    pool_left_ = bytes;
+  }
   template <class T>
   int alloc(T** out, int64_t count, hipStream_t s) {
     *out = nullptr;
-    const size_t bytes = sizeof(T) * (size_t)std::max<int64_t>(count, 1);
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(out), bytes);
-    if (e != hipSuccess) return hfail(e, "hipMalloc(compression)");
-    ptrs_.push_back(*out);
+    const size_t bytes = sizeof(T) * (size_t)std::max<int64_t>(count, 1), room = (bytes + 255) / 256 * 256;
+    if (room <= pool_left_) {
+      *out = reinterpret_cast<T*>(pool_);
+      pool_ += room;
+      pool_left_ -= room;
+    } else {
+      hipError_t e = hipMalloc(reinterpret_cast<void**>(out), bytes);
+      if (e != hipSuccess) return hfail(e, "hipMalloc(compression)");
+      ptrs_.push_back(*out);
+    }
     reg(*out, bytes);
     CK(hipMemsetAsync(*out, 0, bytes, s), "hipMemsetAsync(compression)");
     return H2_OK;
@@ -98,8 +117,12 @@ class Arena {
     if (!p || ld < rows) return false;
     const uintptr_t a = reinterpret_cast<uintptr_t>(p);
     const uintptr_t b = reinterpret_cast<uintptr_t>(p + (rows - 1) + (cols - 1) * ld) + sizeof(double);
-    for (const auto& r : regions_)
-      if (a >= r.first && b <= r.second) return true;
+    if (last_ < regions_.size() && a >= regions_[last_].first && b <= regions_[last_].second) return true;
+    for (size_t i = 0; i < regions_.size(); ++i)
+      if (a >= regions_[i].first && b <= regions_[i].second) {
+        last_ = i;
+        return true;
+      }
     return false;
   }
 
@@ -110,6 +133,9 @@ class Arena {
   static constexpr size_t kChunk = size_t(16) << 20;
   uint8_t* chunk_ = nullptr;
   size_t used_ = 0;
+  uint8_t* pool_ = nullptr;  // reserve()
+  size_t pool_left_ = 0;
+  mutable size_t last_ = 0;  // the region of the last operand found
 };
 
 int oob(const char* what) {
@@ -711,6 +737,15 @@ int compress_impl(h2_op_s* h, double tau, hipStream_t s, h2_handle* out, h2_comp
   C.S = base + oS;
   Sizes old = sizes_of(P, std::vector<int64_t>(P.krow, P.krow + q + 1), std::vector<int64_t>(P.kcol, P.kcol + q + 1),
                        sep);
+  {
+    // the arrays below, the per-level scratch and uploads (an eighth more), all but
+    // the coupling copy where that is large
+    const int64_t per = 6 * C.tot_k2 + 2 * C.tot_k + 2 * C.tot_stack + P.nnodes;
+    int64_t all = per * (sep ? 2 : 1) + 4 * old.U + 3 * old.E + (sep ? 4 * old.V + 3 * old.F : 0);
+    all += all / 8 + (int64_t)(48 << 20) / 8;
+    if (old.S <= all) all += 2 * old.S;
+    C.ar.reserve(sizeof(double) * (size_t)all);
+  }
   RC(C.ar.alloc(&C.So, old.S, s));
   Tree Xr, Xc;
   Xr.k = P.krow; Xr.B = base; Xr.T = base + oE; Xr.tbase = &P.ebase;

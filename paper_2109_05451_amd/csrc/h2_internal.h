@@ -297,19 +297,25 @@ void emit_rows_N(const OpLayout& L, const RowBases& B, RowsN* R);
 // level below them (or from the points), a downsweep stage adds to y^ of one
 // level (or to the leaf expansion) the parts of several levels above it, with
 // the products of the transfers between them, formed once at load.
-struct ComposeTask {  // dst (m x n) = A (m x k) B (k x n), column-major; k == 0: a copy of A (m x n)
-  int64_t a, b, dst;
-  int32_t m, k, n;
-  int32_t where;  // A in: 0 the matrix array, 1 the transposed array, 2 scratch (as dst: bit 2 set = scratch)
+// The products of one stage, formed on the device: for every node c of level s
+// (every leaf, s = q + 1) the matrices G_l = B_c T_(l+1) .. T_(s-1), l from s - 1
+// down to lo, with B_c its stored transfer (or leaf basis) and T_x the transfer
+// of its ancestor on level x.  Downsweep: G_l, l = s - 1 .. lo, side by side at
+// reg[0] onwards, node by node; upsweep: the transposes of G_l, l < s - 1, at
+// reg[l] onwards (elements of the operator's transposed array).
+struct ComposeStage {
+  int32_t s, lo, points, up;
+  int64_t c0, count;  // first node and their number
+  int64_t stored;     // matrix array: leaf bases (points), else the transfers of level s
+  std::vector<int64_t> k, tr, reg;  // per level: rank; matrix array offset of its transfers; output
 };
 struct Composed {
   std::vector<std::vector<RowSpec>> up, down;  // per stage, in running order
   std::vector<char> up_split, down_split;      // the stage has rows of several levels
   std::vector<RowSpec> out;                    // leaf expansion
   bool out_split = false;
-  std::vector<std::vector<ComposeTask>> steps;  // in running order; offsets relative to the operator's arrays
-  std::vector<TransTask> trans;                 // scratch -> transposed array, after the steps
-  int64_t ntrans = 0, nscratch = 0;             // elements of the transposed array (composed rows included) and scratch
+  std::vector<ComposeStage> stages;  // their products, for run_compose
+  int64_t ntrans = 0;                // elements of the transposed array, composed rows included
 };
 // op 'N' (or 'T': trans_op) rows at the bases B; the composed matrices go to
 // the operator's transposed array from element `first` on.
@@ -386,8 +392,10 @@ struct h2_op_s {
   h2_stats_t stats{};
   std::vector<h2_level_stats_t> level_stats;
   // device data
+  void* d_base = nullptr;     // the allocation behind d_mat and d_trans
+  void* d_index = nullptr;    // the allocation behind every index array
   double* d_mat = nullptr;    // U, E, V, F, S, D (section layout of the buffer kept)
-  double* d_trans = nullptr;  // transposed copies: U^T, E^T (and V^T, F^T)
+  double* d_trans = nullptr;  // transposed copies: U^T, E^T (and V^T, F^T), then the composed sweep rows
   int64_t n_lowrank = 0;      // elements of d_mat before the dense section (U, E, V, F, S)
   int64_t n_trans = 0;        // elements of d_trans
   float* d_mat32 = nullptr;   // FP32 copies of d_mat[0, n_lowrank) and of d_trans
@@ -498,11 +506,8 @@ hipError_t launch_to_f32(const double* src, float* dst, int64_t n, hipStream_t s
 // task's block of `mat` transposed into `trans` (which the caller zeroed).
 hipError_t launch_transpose_tasks(const TransTask* tasks, int64_t ntasks, const double* mat, double* trans,
                                   hipStream_t s);
-// One step of composed transfers: every task's product (or copy).
-hipError_t launch_compose_tasks(const ComposeTask* tasks, int64_t ntasks, const double* mat, double* trans,
-                                double* scratch, hipStream_t s);
-// Every task list of `C` on the device (synchronous): H2_OK, H2_ENOMEM, H2_EHIP.
-int run_compose(const Composed& C, const double* mat, double* trans);
+// Forms every stage's products on the device (synchronous): H2_OK, H2_ENOMEM, H2_EHIP.
+int run_compose(const std::vector<const Composed*>& C, const Parsed& P, const double* mat, double* trans);
 // BF16 path (data: __bf16, rows stored row-major; see the kernel file)
 hipError_t launch_rows_mfma_bf16(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
                                  const void* data, const void* in, bool in16, int64_t ldb, void* out, bool out16,

@@ -37,60 +37,91 @@ hipError_t launch_transpose_tasks(const TransTask* tasks, int64_t ntasks, const 
 }
 
 namespace {
-// One workgroup per task; the operands are a few KB and stay in L1/L2 (a load-
-// time kernel: a few ms for the largest operators).
-__global__ __launch_bounds__(256) void k_compose_tasks(const ComposeTask* __restrict__ tasks, const double* mat,
-                                                       double* trans, double* scratch) {
-  const ComposeTask t = tasks[blockIdx.x];
-  const int w = t.where & 3;
-  const double* A = (w == 0 ? mat : w == 1 ? trans : scratch) + t.a;
-  const double* B = mat + t.b;
-  double* C = (t.where & 4 ? scratch : trans) + t.dst;
-  for (int e = threadIdx.x; e < t.m * t.n; e += 256) {
-    const int r = e % t.m, c = e / t.m;
-    double s = 0.0;
-    if (t.k == 0) s = A[e];
-    for (int i = 0; i < t.k; ++i) s += A[r + (int64_t)t.m * i] * B[i + (int64_t)t.k * c];
-    C[e] = s;
+// One stage of run_compose, a workgroup per node: its matrices one level after
+// the other, each read back from where it was written (a few KB, in L1/L2).
+// tab: per level ranks, transfer offsets, first nodes, outputs (nl each).
+// Run once at load: well under a millisecond for 2^16 points.
+__global__ __launch_bounds__(256) void k_compose(const int64_t* __restrict__ tab, int nl,
+                                                 const int32_t* __restrict__ parent, const int32_t* __restrict__ lo_of,
+                                                 int64_t leaf0, int s, int lo, int points, int up, int64_t c0,
+                                                 int64_t stored, const double* __restrict__ mat, double* trans) {
+  const int64_t *k = tab, *tr = tab + nl, *lp = tab + 2 * nl, *reg = tab + 3 * nl;
+  const int64_t c = c0 + blockIdx.x;
+  const int top = s - 1, q = nl - 1;
+  const int64_t p0 = points ? lo_of[c - leaf0] : 0;
+  const int m = points ? lo_of[c - leaf0 + 1] - (int)p0 : (int)k[s];
+  const int64_t before = points ? p0 : blockIdx.x * (int64_t)k[s];  // rows of the nodes before this one
+  const double* A = mat + stored + (points ? p0 * k[q] : blockIdx.x * (int64_t)(k[s] * k[top]));
+  bool trA = false;  // A holds the transpose
+  int64_t sum = 0;
+  for (int l = lo; l <= top; ++l) sum += k[l];
+  double* D = trans + reg[0] + before * sum;  // downsweep: this node's matrices
+  int64_t a = points ? c : parent[c];         // ancestor on level l + 1
+  if (!up) {
+    for (int e = threadIdx.x; e < m * (int)k[top]; e += 256) D[e] = A[e];
+    A = D;
+    D += m * k[top];
+    __syncthreads();
+  }
+  for (int l = top - 1; l >= lo; --l) {
+    const int kk = (int)k[l + 1], kn = (int)k[l];
+    const double* T = mat + tr[l + 1] + (a - lp[l + 1]) * (int64_t)(kk * kn);
+    double* C = up ? trans + reg[l] + before * kn : D;
+    for (int e = threadIdx.x; e < m * kn; e += 256) {
+      const int r = up ? e / kn : e % m, j = up ? e % kn : e / m;
+      double sum_ = 0.0;
+      for (int i = 0; i < kk; ++i) sum_ += (trA ? A[i + (int64_t)kk * r] : A[r + (int64_t)m * i]) * T[i + (int64_t)kk * j];
+      C[e] = sum_;
+    }
+    __syncthreads();  // this level's matrix is the next one's operand
+    A = C;
+    trA = up;
+    D += (int64_t)m * kn;
+    a = parent[a];
   }
 }
 }  // namespace
 
-hipError_t launch_compose_tasks(const ComposeTask* tasks, int64_t ntasks, const double* mat, double* trans,
-                                double* scratch, hipStream_t s) {
-  if (ntasks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_compose_tasks, dim3((unsigned)ntasks), dim3(256), 0, s, tasks, mat, trans, scratch);
-  return hipGetLastError();
-}
-
-int run_compose(const Composed& C, const double* mat, double* trans) {
-  // one device buffer: the tasks of every step, the transpositions, scratch
-  size_t ntask = 0;
-  for (const auto& v : C.steps) ntask += v.size();
-  if (ntask == 0) return H2_OK;
-  const size_t tb = sizeof(ComposeTask) * ntask, sb = sizeof(TransTask) * C.trans.size();
-  std::vector<char> host(tb + sb);
-  size_t at = 0;
-  for (const auto& v : C.steps) {
-    if (!v.empty()) std::memcpy(host.data() + at, v.data(), sizeof(ComposeTask) * v.size());
-    at += sizeof(ComposeTask) * v.size();
-  }
-  if (sb) std::memcpy(host.data() + tb, C.trans.data(), sb);
-  const size_t scratch_at = (tb + sb + 255) / 256 * 256;
+int run_compose(const std::vector<const Composed*>& C, const Parsed& P, const double* mat, double* trans) {
+  // one device buffer: per stage the level tables, then the tree
+  const int nl = (int)P.q + 1;
+  size_t nst = 0;
+  for (const Composed* c : C) nst += c->stages.size();
+  if (nst == 0) return H2_OK;
+  const size_t tabs = sizeof(int64_t) * 4 * nl * nst, pb = sizeof(int32_t) * P.nnodes;
+  std::vector<char> host(tabs + pb + sizeof(int32_t) * (P.nleaves + 1));
+  int64_t* t = reinterpret_cast<int64_t*>(host.data());
+  for (const Composed* c : C)
+    for (const ComposeStage& g : c->stages) {
+      for (int l = 0; l < nl; ++l) {
+        t[l] = g.k[l];
+        t[nl + l] = g.tr[l];
+        t[2 * nl + l] = P.level_ptr[l];
+        t[3 * nl + l] = g.reg[l];
+      }
+      t += 4 * nl;
+    }
+  int32_t* par = reinterpret_cast<int32_t*>(host.data() + tabs);
+  for (int64_t c = 0; c < P.nnodes; ++c) par[c] = (int32_t)P.parent[c];
+  int32_t* lo = par + P.nnodes;
+  for (int64_t i = 0; i < P.nleaves; ++i) lo[i] = (int32_t)P.lo[P.leaf0 + i];
+  lo[P.nleaves] = (int32_t)P.n;
   char* d = nullptr;
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&d), scratch_at + sizeof(double) * (size_t)C.nscratch + 256);
-  if (e == hipSuccess) e = hipMemcpy(d, host.data(), tb + sb, hipMemcpyHostToDevice);
-  double* scratch = reinterpret_cast<double*>(d + scratch_at);
-  at = 0;
-  for (const auto& v : C.steps) {  // in stream order: a step reads what the one before it wrote
-    if (e == hipSuccess)
-      e = launch_compose_tasks(reinterpret_cast<const ComposeTask*>(d) + at, (int64_t)v.size(), mat, trans, scratch,
-                               nullptr);
-    at += v.size();
-  }
-  if (e == hipSuccess && sb)
-    e = launch_transpose_tasks(reinterpret_cast<const TransTask*>(d + tb), (int64_t)C.trans.size(), scratch, trans,
-                               nullptr);
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&d), host.size());
+  if (e == hipSuccess) e = hipMemcpy(d, host.data(), host.size(), hipMemcpyHostToDevice);
+  size_t at = 0;
+  for (const Composed* c : C)
+    for (const ComposeStage& g : c->stages) {
+      if (e == hipSuccess && g.count > 0) {
+        hipLaunchKernelGGL(k_compose, dim3((unsigned)g.count), dim3(256), 0, nullptr,
+                           reinterpret_cast<const int64_t*>(d) + 4 * nl * at, nl,
+                           reinterpret_cast<const int32_t*>(d + tabs),
+                           reinterpret_cast<const int32_t*>(d + tabs) + P.nnodes, P.leaf0, g.s, g.lo, g.points, g.up,
+                           g.c0, g.stored, mat, trans);
+        e = hipGetLastError();
+      }
+      ++at;
+    }
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (d) (void)hipFree(d);
   if (e == hipSuccess) return H2_OK;

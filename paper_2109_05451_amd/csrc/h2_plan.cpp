@@ -227,9 +227,20 @@ void compose_sweeps(const OpLayout& L, const RowBases& B, bool trans_op, int64_t
   const int64_t lmin = std::min(first_coupling_level(P), q);
   int64_t ext = first;
   auto msz = [&](int64_t c) { return (int32_t)(P.hi[c] - P.lo[c]); };
-  auto task = [&](size_t depth, const ComposeTask& t) {
-    if (C->steps.size() <= depth) C->steps.resize(depth + 1);
-    if (t.m > 0 && t.n > 0) C->steps[depth].push_back(t);
+  auto stage_of = [&](const Basis& b, int64_t s, int64_t lo, bool up) {
+    ComposeStage g{};
+    g.s = (int32_t)s;
+    g.lo = (int32_t)lo;
+    g.points = s > q;
+    g.up = up;
+    g.c0 = s > q ? lp[q] : lp[s];
+    g.count = s > q ? lp[q + 1] - lp[q] : lp[s + 1] - lp[s];
+    g.stored = s > q ? b.leaf : b.tr + (*b.base)[s];
+    g.k.assign(b.k, b.k + q + 1);
+    g.tr.assign(q + 1, 0);
+    for (int64_t l = 1; l <= q; ++l) g.tr[l] = b.tr + (*b.base)[l];
+    g.reg.assign(q + 1, 0);
+    return g;
   };
   const std::vector<int64_t> su = sweep_stages(P, bu.k, lmin, true, group),
                              sd = sweep_stages(P, bd.k, lmin, false, group);
@@ -253,41 +264,34 @@ void compose_sweeps(const OpLayout& L, const RowBases& B, bool trans_op, int64_t
         rows.push_back(std::move(r));
       }
     }
-    // the levels above: transposes of G[c][l] = G[c][l + 1] F_(ancestor of c on level l + 1)
-    std::vector<int64_t> anc(c1 - c0), g(c1 - c0);  // ancestor on level l + 1; G[c][l + 1] (matrix array, then scratch)
-    for (int64_t c = c0; c < c1; ++c) {
-      anc[c - c0] = pts ? c : P.parent[c];
-      g[c - c0] = pts ? bu.leaf + P.lo[c] * bu.k[q] : bu.tr + bu.at(c, s);
-    }
+    if (lo == top) continue;
+    // the levels above: transposes of the composed matrices, a node's
+    // descendants side by side
+    ComposeStage g = stage_of(bu, s, lo, true);
+    std::vector<int64_t> anc(c1 - c0);  // ancestor on level l + 1
+    for (int64_t c = c0; c < c1; ++c) anc[c - c0] = pts ? c : P.parent[c];
     for (int64_t l = top - 1; l >= lo; --l) {
-      int64_t at = ext;  // rows of level l, node by node, their descendants' blocks in order
+      g.reg[l] = ext;
       int64_t c = c0;
       for (int64_t p = lp[l]; p < lp[l + 1]; ++p) {
-        RowSpec r{B.trans + at, B.xh + L.hoff[p], B.ld_h, pts ? B.ld_x : B.ld_h, (int32_t)bu.k[l], {}};
-        if (pts) r.blks.push_back({0, B.xt + P.lo[p], msz(p), 0});
-        for (; c < c1; ++c) {
-          const int64_t a = anc[c - c0];  // on level l + 1
-          if (P.parent[a] != p) break;
-          const int32_t m = pts ? msz(c) : (int32_t)bu.k[s];
-          const int64_t d = C->nscratch;
-          C->nscratch += (int64_t)m * bu.k[l];
-          task((size_t)(top - 1 - l), {g[c - c0], bu.tr + bu.at(a, l + 1), d, m, (int32_t)bu.k[l + 1], (int32_t)bu.k[l],
-                                       (l == top - 1 ? 0 : 2) | 4});
-          if (m > 0) C->trans.push_back({d, at, m, (int32_t)bu.k[l]});
-          at += (int64_t)m * bu.k[l];
-          if (!pts) {
-            // consecutive descendants are consecutive rows of x^ where the level's tree rows are all used
-            const int64_t in = B.xh + L.hoff[c];
-            if (!r.blks.empty() && r.blks.back().in_off + r.blks.back().width == in) r.blks.back().width += m;
-            else r.blks.push_back({0, in, m, 0});
-          }
-          g[c - c0] = d;
+        RowSpec r{B.trans + ext, B.xh + L.hoff[p], B.ld_h, pts ? B.ld_x : B.ld_h, (int32_t)bu.k[l], {}};
+        if (pts) {
+          r.blks.push_back({0, B.xt + P.lo[p], msz(p), 0});
+          ext += (P.hi[p] - P.lo[p]) * bu.k[l];
+        }
+        for (; c < c1 && P.parent[anc[c - c0]] == p; ++c) {
           anc[c - c0] = p;
+          if (pts) continue;
+          ext += bu.k[s] * bu.k[l];
+          // consecutive descendants are consecutive rows of x^ where all the level's tree rows are used
+          const int64_t in = B.xh + L.hoff[c];
+          if (!r.blks.empty() && r.blks.back().in_off + r.blks.back().width == in) r.blks.back().width += (int32_t)bu.k[s];
+          else r.blks.push_back({0, in, (int32_t)bu.k[s], 0});
         }
         rows.push_back(std::move(r));
       }
-      ext = at;
     }
+    C->stages.push_back(std::move(g));
   }
   // ---- downsweep, from the root towards the points
   for (size_t i = sd.size() - 1; i-- > 0;) {
@@ -295,27 +299,18 @@ void compose_sweeps(const OpLayout& L, const RowBases& B, bool trans_op, int64_t
     const bool pts = s > q, split = lo < top;
     std::vector<RowSpec> rows;
     const int64_t c0 = pts ? lp[q] : lp[s], c1 = pts ? lp[q + 1] : lp[s + 1];
+    if (split) {
+      C->stages.push_back(stage_of(bd, s, lo, false));
+      C->stages.back().reg[0] = ext;
+    }
     for (int64_t c = c0; c < c1; ++c) {
       const int32_t m = pts ? msz(c) : (int32_t)bd.k[s];
-      const int64_t stored = pts ? bd.leaf + P.lo[c] * bd.k[q] : bd.tr + bd.at(c, s);
-      RowSpec r{split ? B.trans + ext : B.mat + stored, pts ? B.zn + P.lo[c] : B.yh + L.hoff[c], pts ? B.ld_x : B.ld_h,
-                B.ld_h, m, {}};
+      RowSpec r{split ? B.trans + ext : B.mat + (pts ? bd.leaf + P.lo[c] * bd.k[q] : bd.tr + bd.at(c, s)),
+                pts ? B.zn + P.lo[c] : B.yh + L.hoff[c], pts ? B.ld_x : B.ld_h, B.ld_h, m, {}};
       int64_t a = pts ? c : P.parent[c];  // ancestor on level l
-      int64_t prev = stored;
       for (int64_t l = top; l >= lo; --l) {
         r.blks.push_back({0, B.yh + L.hoff[a], (int32_t)bd.k[l], 0});
-        if (split) {
-          if (l == top) {
-            task(0, {stored, 0, ext, m, 0, (int32_t)bd.k[l], 0});
-          } else {
-            // a is the ancestor on level l; the transfer used is its child's on the path
-            int64_t ch = pts ? c : P.parent[c];
-            for (int64_t x = top; x > l + 1; --x) ch = P.parent[ch];
-            task((size_t)(top - l), {prev, bd.tr + bd.at(ch, l + 1), ext, m, (int32_t)bd.k[l + 1], (int32_t)bd.k[l], 1});
-          }
-          prev = ext;
-          ext += (int64_t)m * bd.k[l];
-        }
+        if (split) ext += (int64_t)m * bd.k[l];
         if (l > lo) a = P.parent[a];
       }
       rows.push_back(std::move(r));
