@@ -756,6 +756,21 @@ int load_common(const uint8_t* buf, int64_t len, int device, h2_handle* out, con
 // adds only exact zeros and does not run.
 bool skipped(const h2_op_s* h, const Launch& L) { return L.level >= 0 && L.level < h->lmin; }
 
+// Dense rows of operators of few leaves on the multi-vector path: a workgroup
+// per row, its columns split over the four waves.  With a wave per row they
+// are one or two waves per SIMD, too few to cover the loads, and the longest
+// row is what the product waits for.  Whole products in us, a wave per row
+// against this: 20 000 points 140 / 113 (16 vectors), 3D of 20 000 points
+// 600 / 546, of 131 072 (leaf 64, 64 vectors) 3400 / 3200, of 60 000 in FP32
+// (64 vectors) 1795 / 1454.  From 2048 leaves in 2D on the two are within 2%
+// (131 072 points 413 / 407 and 810 / 826, 262 144 points 757 / 750), and at
+// 16 384 leaves a wave per row leaves the slots to the sweeps; the line is
+// drawn where the dense rows fill the GPU eight times over.
+constexpr int64_t kDenseSplit = 8192;
+bool dense_split(const h2_op_s* h, const Launch& L) {
+  return !L.lowrank && L.kind == KIND_STREAM && L.max_rows <= 64 && h->nleaves < kDenseSplit;
+}
+
 int run_launch(h2_op_s* h, const Workspace& w, const Launch& L, int nv, const Epilogue& ep, hipStream_t s,
                int nvp = 0, int mode_override = -1, int prec = H2_PREC_FP64, bool x32 = false,
                double* out_ptr = nullptr) {
@@ -797,9 +812,12 @@ int run_launch(h2_op_s* h, const Workspace& w, const Launch& L, int nv, const Ep
     kcw = f.kc;
     occ = f.occ;
   }
-  if (nvp > 0 && L.split && L.max_rows <= 64) {
+  if (nvp > 0 && dense_split(h, L)) {
     e = launch_split_rows(h->rt.d_rows + L.row_begin, L.row_count, h->rt.d_colend, h->rt.d_in_off, data, bufs[L.in],
-                          out, nvp, mode, L.max_rows, s);
+                          out, nvp, mode, L.min_rows, L.max_rows, s, true, grid_of, L.remapp[H2_PREC_FP64]);
+  } else if (nvp > 0 && L.split && L.max_rows <= 64) {
+    e = launch_split_rows(h->rt.d_rows + L.row_begin, L.row_count, h->rt.d_colend, h->rt.d_in_off, data, bufs[L.in],
+                          out, nvp, mode, L.min_rows, L.max_rows, s);
   } else if (nvp > 0 && L.kind == KIND_GATHER) {
     e = launch_wave_cols(h->gt.d_rows + L.row_begin, L.row_count, h->gt.d_data, h->gt.d_mr, h->gt.d_in_off, data,
                          bufs[L.in], out, nvp, L.max_rows, s);
@@ -879,7 +897,7 @@ int prepare_fl(h2_op_s* h, int prec) {
     keys.reserve(2 * h->rt.rows.size());
     int64_t n_fl = 0;
     each_launch(h->planN, [&](Launch& L) {
-      if (L.kind == KIND_STREAM && !L.split)
+      if (L.kind == KIND_STREAM && !L.split && !dense_split(h, L))
         place_fl(h->rt, L.row_begin, L.row_begin + L.row_count, L.arr, &keys, &n_fl);
     });
     if (!h->rt.rows.empty())
@@ -894,7 +912,7 @@ int prepare_fl(h2_op_s* h, int prec) {
   auto make = [&](void* d, bool fp32) -> hipError_t {
     hipError_t e = hipSuccess;
     auto one = [&](const Launch& L) {
-      if (e != hipSuccess || L.split || (fp32 && !L.lowrank)) return;  // the dense rows stay FP64
+      if (e != hipSuccess || L.split || dense_split(h, L) || (fp32 && !L.lowrank)) return;  // the dense rows stay FP64
       if (fp32)
         e = launch_rows_to_fl<float>(h->rt.d_rows + L.row_begin, L.row_count, h->rt.d_colend,
                                      L.arr == ARR_TRANS ? h->d_trans32 : h->d_mat32, static_cast<float*>(d), nullptr);
@@ -937,6 +955,7 @@ int drop_unused_fl(h2_op_s* h) {
   std::lock_guard<std::mutex> lock(h->prep_mu);
   bool use64 = false, use32 = false;
   auto look = [&](const Launch& L) {
+    if (L.split || dense_split(h, L)) return;
     auto reads = [&](int p) { return (L.kcp[p] == kWaveRows || L.kcp[p] == kWaveTiles) && L.flp[p] != 0; };
     use64 = use64 || reads(H2_PREC_FP64);
     use32 = use32 || (L.lowrank && reads(H2_PREC_FP32));
@@ -1559,6 +1578,7 @@ int h2_tune(h2_handle h, int64_t nv, int prec, void* stream) {
           // the dense rows run beside the sweeps: a persistent grid would hold
           // every CU slot and starve them, so they keep one workgroup per row
           if (g != 0 && !L.lowrank) continue;
+          if (dense_split(h, L) && (kc != kWaveRows || cand > 1)) continue;  // one form
           Launch T = L;
           T.kcp[pi] = kc;
           T.gridp[pi] = g;

@@ -548,11 +548,12 @@ struct RowForm {
   int kc, occ;
 };
 RowForm auto_form(int nvp, int64_t rows, int max_rows);
-// Composed sweep rows (FP64, at most 64 outputs): a workgroup per row and
-// 16-vector tile, the columns split over its four waves
+// FP64 rows of at most 64 outputs, the columns split over a workgroup's four
+// waves: a workgroup per row and 16-vector tile (composed sweep rows), or (all)
+// per row, which reads the matrix once (dense rows of operators of few leaves)
 hipError_t launch_split_rows(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
-                             const double* data, const double* in, double* out, int nvp, int mode, int max_rows,
-                             hipStream_t s);
+                             const double* data, const double* in, double* out, int nvp, int mode, int min_rows,
+                             int max_rows, hipStream_t s, bool all = false, int64_t grid = 0, int remap = 0);
 // True when launch_wave_rows has a second form (occ != 0) for this pass width
 inline bool wave_alt(int nvp, bool narrow) { return nvp != 48 && !narrow; }
 // dst[R.fl_off ...] = the fragment-ordered copy of every row's matrix at src[R.data_off ...]

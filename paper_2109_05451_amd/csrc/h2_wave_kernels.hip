@@ -69,9 +69,11 @@ constexpr int kChunk = 1024;  // columns of one source-row table (4 KB of LDS pe
 // row's empty tiles are skipped (cheaper than loading them, though the waits
 // then count the fewer).
 // KS: a workgroup per row and vector range, the row's columns in four equal
-// pieces, one per wave, the partial sums added through LDS in wave order: the
-// composed sweep rows, few and long, where one wave's chain of loads is what
-// the launch waits for.
+// pieces, one per wave, the partial sums added through LDS in wave order, one
+// vector tile at a time (32 KB at most, over the source-row tables): the
+// composed sweep rows and the dense rows of operators of few leaves, where one
+// wave's chain of loads is what the launch waits for.  Dense rows of a 3D
+// operator of 131 072 points at 64 vectors: 0.73 -> 0.60 ms per half.
 template <typename T, int NT, int NTW, int NF, int TQ, int U, int W, bool FL, bool WHOLE, bool KS = false>
 __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__ rows, int64_t nrows,
                                                      const int32_t* __restrict__ colend,
@@ -88,17 +90,17 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
   constexpr int ES = sizeof(T);
   typedef const __attribute__((address_space(1))) char* gptr;
   static_assert((U == 2 || U % 4 == 0) && kChunk % G == 0, "load groups");
-  constexpr int LDP = 16 * NTW;  // LDS row of the partial sums
-  __shared__ __align__(16) double part[KS ? 4 * (16 * NF + 4 * TQ) * LDP : 1];
   // source rows of a chunk's columns; a lane's U steps of a group adjacent,
-  // and two groups of padding for the reads ahead
-  __shared__ __align__(16) uint32_t s_src[4][kChunk + 2 * G];
+  // and two groups of padding for the reads ahead.  KS: afterwards the four
+  // waves' partial sums of one vector tile
+  constexpr int SRC = kChunk + 2 * G, PART = KS ? 4 * (16 * NF + 4 * TQ) * 16 * 2 : 0;
+  __shared__ __align__(16) uint32_t s_mem[4 * SRC > PART ? 4 * SRC : PART];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int slot = KS ? 0 : wave / WPR, vt0 = KS ? (int)(blockIdx.x % WPR) * NTW : (wave % WPR) * NTW;
   const int arow = lane & 15, akk = lane >> 4;
   const int vcol = 16 * vt0 + (BV ? NTW * arow : arow);  // first vector of the lane
-  uint32_t* src = s_src[wave];
+  uint32_t* src = s_mem + wave * SRC;
   const double* inl = in + vcol;
   // rows by workgroup: grid-stride, or (remap; a grid of a multiple of 8)
   // each XCD (workgroups b with the same b % 8) takes one contiguous eighth
@@ -106,9 +108,10 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
   // the row order and their shared input segments meet in that XCD's L2
   const int64_t per = remap ? (nrows + 7) / 8 : nrows;
   const int64_t base = remap ? (int64_t)(blockIdx.x % 8) * per : 0;
-  const int64_t wg = KS ? blockIdx.x / WPR : remap ? blockIdx.x / 8 : blockIdx.x;
-  const int64_t nwg = remap ? gridDim.x / 8 : gridDim.x;
-  for (int64_t jr = KS ? wg : wg * RPW + slot; jr < per; jr += KS ? nrows : nwg * RPW) {
+  // (KS: the vector ranges of a row in neighbouring workgroups; remap only with one range)
+  const int64_t wg = remap ? blockIdx.x / 8 : KS ? blockIdx.x / WPR : blockIdx.x;
+  const int64_t nwg = remap ? gridDim.x / 8 : KS ? gridDim.x / WPR : gridDim.x;
+  for (int64_t jr = wg * RPW + slot; jr < per; jr += nwg * RPW) {
     const int64_t ri = base + jr;
     if (ri >= nrows) break;
     const RowDesc R = rows[ri];
@@ -322,22 +325,63 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
       sbase = (gptr)(data + (FL ? R.fl_off : R.data_off)) + (int64_t)m * ES * (c0 + kChunk);
     }
 
+    // matrix row of accumulator element r of tile t, and of tail t
+    auto row_of = [&](int t, int r) __attribute__((always_inline)) {
+      const int i = Mfma<T>::row(r, akk);
+      return FL || (t == NF - 1 && NF % 2 == 1) ? 16 * t + i : 32 * (t / 2) + 2 * i + (t & 1);
+    };
+    auto row_of_tail = [&](int t) __attribute__((always_inline)) {
+      return 16 * NF + (FL || TQ == 1 ? 4 * t + akk : 2 * akk + t);
+    };
+    if constexpr (KS) {
+      // one vector tile after the other through LDS
+      double* part = reinterpret_cast<double*>(s_mem);
+#pragma unroll
+      for (int j = 0; j < NTW; ++j) {
+        __syncthreads();  // the source rows, or the tile before this one, are read
+#pragma unroll
+        for (int t = 0; t < NF; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = row_of(t, r);
+            if (row < m) part[(wave * m + row) * 16 + arow] = acc[t][j][r];
+          }
+        if constexpr (TQ > 0) {
+#pragma unroll
+          for (int t = 0; t < TQ; ++t) {
+            const int row = row_of_tail(t);
+            if (row < m) part[(wave * m + row) * 16 + arow] = acc4[t][j];
+          }
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < 16 * m; e += kT) {
+          double sum = part[e];
+#pragma unroll
+          for (int w = 1; w < 4; ++w) sum += part[16 * w * m + e];
+          const int v = e & 15;
+          double* o = out + (R.out_off + (e >> 4)) * NVP + 16 * vt0 + (BV ? NTW * v + j : 16 * j + v);
+          *o = mode == MODE_STORE ? sum : *o + sum;
+        }
+      }
+      __syncthreads();
+      continue;
+    }
     // stores: vectors vcol + j (NTW even) or vcol + 16 j of the tile's rows
     auto put = [&](int row, auto val) __attribute__((always_inline)) {
       if (row >= m) return;
-      double* o = KS ? part + (wave * m + row) * LDP + vcol - 16 * vt0 : out + (R.out_off + row) * NVP + vcol;
+      double* o = out + (R.out_off + row) * NVP + vcol;
       if constexpr (BV) {
 #pragma unroll
         for (int j = 0; j < NTW; j += 2) {
           v2 v = {val(j), val(j + 1)};
           v2* p = reinterpret_cast<v2*>(o + j);
-          if (!KS && mode != MODE_STORE) v += *p;
+          if (mode != MODE_STORE) v += *p;
           *p = v;
         }
       } else {
 #pragma unroll
         for (int j = 0; j < NTW; ++j) {
-          if (KS || mode == MODE_STORE) o[16 * j] = val(j);
+          if (mode == MODE_STORE) o[16 * j] = val(j);
           else o[16 * j] += val(j);
         }
       }
@@ -345,26 +389,10 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
 #pragma unroll
     for (int t = 0; t < NF; ++t)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = Mfma<T>::row(r, akk);
-        put(FL || (t == NF - 1 && NF % 2 == 1) ? 16 * t + i : 32 * (t / 2) + 2 * i + (t & 1),
-            [&](int j) { return (double)acc[t][j][r]; });
-      }
+      for (int r = 0; r < 4; ++r) put(row_of(t, r), [&](int j) { return (double)acc[t][j][r]; });
     if constexpr (TQ > 0) {
 #pragma unroll
-      for (int t = 0; t < TQ; ++t)
-        put(16 * NF + (FL || TQ == 1 ? 4 * t + akk : 2 * akk + t), [&](int j) { return acc4[t][j]; });
-    }
-    if constexpr (KS) {
-      __syncthreads();
-      for (int e = threadIdx.x; e < m * LDP; e += kT) {
-        const int row = e / LDP, v = e % LDP;
-        double sum = part[row * LDP + v];
-#pragma unroll
-        for (int w = 1; w < 4; ++w) sum += part[(w * m + row) * LDP + v];
-        double* o = out + (R.out_off + row) * NVP + 16 * vt0 + v;
-        *o = mode == MODE_STORE ? sum : *o + sum;
-      }
+      for (int t = 0; t < TQ; ++t) put(row_of_tail(t), [&](int j) { return acc4[t][j]; });
     }
   }
 }
@@ -653,18 +681,22 @@ struct SplitArgs {
   const int64_t* in_off;
   const double *data, *in;
   double* out;
-  int mode;
+  int mode, min_rows, remap;
+  int64_t grid;
   hipStream_t s;
 };
 
 template <int NT, int NTW, int NF, int TQ, int U>
 void launch_split_form(const SplitArgs& A) {
-  constexpr int W0 = form_waves(form_regs(8, NTW, NF, TQ, U));
-  constexpr int LDS = 4 * (16 * NF + 4 * TQ) * 16 * NTW * 8 + 4 * (kChunk + 8 * U) * 4;
-  constexpr int W = W0 * LDS <= 160 * 1024 ? W0 : 2;  // workgroups per CU that the LDS holds
-  hipLaunchKernelGGL((k_wave_rows<double, NT, NTW, NF, TQ, U, W, false, false, true>),
-                     dim3((unsigned)(A.nrows * (NT / NTW))), dim3(kT), 0, A.s, A.rows, A.nrows, A.colend, A.in_off,
-                     A.data, A.in, A.out, A.mode, 0);
+  constexpr int W = form_waves(form_regs(8, NTW, NF, TQ, U));
+  const dim3 g((unsigned)(wave_grid(A.nrows, 1, A.grid, A.remap) * (NT / NTW))), b(kT);
+  const bool whole = std::min((A.min_rows + 31) / 32 * 2, NF) == NF && (TQ == 0 || A.min_rows > 16 * NF);
+  if (whole)
+    hipLaunchKernelGGL((k_wave_rows<double, NT, NTW, NF, TQ, U, W, false, true, true>), g, b, 0, A.s, A.rows, A.nrows,
+                       A.colend, A.in_off, A.data, A.in, A.out, A.mode, A.remap);
+  else
+    hipLaunchKernelGGL((k_wave_rows<double, NT, NTW, NF, TQ, U, W, false, false, true>), g, b, 0, A.s, A.rows,
+                       A.nrows, A.colend, A.in_off, A.data, A.in, A.out, A.mode, A.remap);
 }
 
 template <int NT, int NTW, int U>
@@ -742,16 +774,18 @@ hipError_t launch_wave_cols(const RowDesc* rows, int64_t nrows, const int64_t* b
 }
 
 hipError_t launch_split_rows(const RowDesc* rows, int64_t nrows, const int32_t* colend, const int64_t* in_off,
-                             const double* data, const double* in, double* out, int nvp, int mode, int max_rows,
-                             hipStream_t s) {
+                             const double* data, const double* in, double* out, int nvp, int mode, int min_rows,
+                             int max_rows, hipStream_t s, bool all, int64_t grid, int remap) {
   if (nrows == 0) return hipSuccess;
   if (max_rows > 64) return hipErrorInvalidValue;
-  const SplitArgs A{rows, nrows, colend, in_off, data, in, out, mode, s};
+  const SplitArgs A{rows, nrows, colend, in_off, data, in, out, mode, min_rows, all || nvp == 16 ? remap : 0, grid, s};
+  // all: one workgroup for a row's whole vector range (the matrix read once),
+  // else one per 16 vectors
   switch (nvp) {
     case 16: launch_split_of<1, 1, 4>(A, max_rows); break;
-    case 32: launch_split_of<2, 1, 4>(A, max_rows); break;
-    case 48: launch_split_of<3, 1, 4>(A, max_rows); break;
-    case 64: launch_split_of<4, 1, 4>(A, max_rows); break;
+    case 32: all ? launch_split_of<2, 2, 4>(A, max_rows) : launch_split_of<2, 1, 4>(A, max_rows); break;
+    case 48: all ? launch_split_of<3, 3, 2>(A, max_rows) : launch_split_of<3, 1, 4>(A, max_rows); break;
+    case 64: all ? launch_split_of<4, 4, 2>(A, max_rows) : launch_split_of<4, 1, 4>(A, max_rows); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
