@@ -196,13 +196,19 @@ int launch_eigs(Ctx& C, const std::vector<EigTask>& tasks) {
   return H2_OK;
 }
 
-template <class T>
-int launch_tasks(Ctx& C, const std::vector<T>& tasks, hipError_t (*fn)(const T*, int64_t, hipStream_t)) {
+template <class T, class F>
+int launch_tasks(Ctx& C, const std::vector<T>& tasks, F fn) {
   if (tasks.empty()) return H2_OK;
   T* d = nullptr;
   RC(C.ar.upload(tasks, &d, C.s));
   CK(fn(d, (int64_t)tasks.size(), C.s), "compression kernel");
   return H2_OK;
+}
+
+int launch_qrs(Ctx& C, const std::vector<QrTask>& tasks) {
+  int me = 0;
+  for (const QrTask& t : tasks) me = std::max(me, t.rows * t.cols);
+  return launch_tasks(C, tasks, [me](const QrTask* d, int64_t n, hipStream_t s) { return launch_qr(d, n, s, me); });
 }
 
 int launch_gemm_tasks(Ctx& C, const std::vector<GemmTask>& tasks, const std::vector<GemmPair>& pairs) {
@@ -291,7 +297,7 @@ int orthogonalize(Ctx& C, Tree& X) {
     qr.push_back(QrTask{A, std::max<int64_t>(mt, 1), Q, std::max<int64_t>(mt, 1), R, std::max<int64_t>(kq, 1),
                         (int32_t)mt, (int32_t)kq});
   }
-  RC(launch_tasks(C, qr, launch_qr));
+  RC(launch_qrs(C, qr));
   for (int64_t l = q; l >= 1; --l) {
     const int64_t kl = X.k[l], kp = X.k[l - 1];
     std::vector<GemmTask> gt;
@@ -317,7 +323,7 @@ int orthogonalize(Ctx& C, Tree& X) {
       qt.push_back(QrTask{st, ld, st, ld, X.R + C.nk2[p], std::max<int64_t>(kp, 1), (int32_t)rows, (int32_t)kp});
     }
     RC(launch_gemm_tasks(C, gt, gp));
-    RC(launch_tasks(C, qt, launch_qr));
+    RC(launch_qrs(C, qt));
     RC(launch_tasks(C, ct, launch_copy));
   }
   return H2_OK;

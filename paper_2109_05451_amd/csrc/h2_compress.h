@@ -93,7 +93,7 @@ struct CopyTask {  // dst (rows x cols) = trans ? src^T : src
   int32_t pad;
 };
 
-hipError_t launch_qr(const QrTask* t, int64_t n, hipStream_t s);
+hipError_t launch_qr(const QrTask* t, int64_t n, hipStream_t s, int max_elems);  // largest rows * cols
 // maxdim: the largest output dimension over the tasks (and, for the triple
 // product, the inner dimension k2); it picks the tile, at most 64
 hipError_t launch_gemm(const GemmTask* t, int64_t n, const GemmPair* p, hipStream_t s, int maxdim);

@@ -23,100 +23,142 @@ namespace {
 constexpr int kCT = 256;  // threads per workgroup
 constexpr int kTile = 64; // largest output rows / columns of one GEMM task
 
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// v + (the lane at the given row rotation's v): the sums of a row of 16 lanes
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+
+// Sum over the wave in every lane, halves first: lanes 32, 16 apart by the
+// lane swaps (both operands the same register: one result holds the lower
+// half's value in both, the other the upper's), then 8, 4, 2, 1 by row
+// rotations.  No LDS: a __shfl_xor of a double is two LDS permutes.
+__device__ __forceinline__ double wave_sum(double v) {
+  const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  v = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  const unsigned lo2 = (unsigned)__double2loint(v), hi2 = (unsigned)__double2hiint(v);
+  const auto l2 = __builtin_amdgcn_permlane16_swap(lo2, lo2, false, false);
+  const auto h2 = __builtin_amdgcn_permlane16_swap(hi2, hi2, false, false);
+  v = __hiloint2double((int)h2[0], (int)l2[0]) + __hiloint2double((int)h2[1], (int)l2[1]);
+  v = dpp_add<0x128>(v);  // row_ror:8
+  v = dpp_add<0x124>(v);
+  v = dpp_add<0x122>(v);
+  return dpp_add<0x121>(v);
 }
 
 // ---------------------------------------------------------------------------
-// Householder QR of an r x c column-major matrix (r * c <= kQrMaxElems).
+// Householder QR of an r x c column-major matrix (r * c <= ELEMS).
 // Reflector j (j < nr = min(r, c)) is H_j = I - tau_j v_j v_j^T with
-// v_j[j] = 1, zeros above j, stored below the diagonal; beta_j = R[j][j].
+// v_j[j] = 1, zeros above j, scal_j times the stored column below it;
+// beta_j = R[j][j].
 // Q (r x c): the first nr columns of H_0 ... H_{nr-1}, zero columns after.
 // R (c x c): upper triangle of the factored matrix in rows < nr, zero rows
 // after (so that A = Q R also when r < c).
+//
+// Bound by the chain of reflectors.  Every wave takes the norm itself and the
+// scale stays beside the column, so a reflector is one barrier; a wave applies
+// it to four columns at a time, whose dot products then overlap; the LDS is
+// sized by the launch's largest operand, so the leaf level is resident at
+// once.  512 stacks of 72 x 36: 231 -> 102 us, 1024 leaf bases of 64 x 36 240 -> 214.
+
+// H_j on columns first + wave, first + wave + 4, ... below last.  Four at a
+// time: past the last column the last one again, whose equal results are
+// stored again, so that no load stands behind a branch.  Rows j + lane and
+// j + lane + 64 stay in registers, further ones (operands of more than 128
+// rows) are read twice.
+__device__ __forceinline__ void reflect(double* sA, int r, int j, double tau, double scal, int first, int last,
+                                        int wave, int lane) {
+  const double* col = sA + j * r;
+  const int i0 = min(j + lane, r - 1), i1 = min(j + lane + 64, r - 1);
+  const bool in0 = j + lane < r, in1 = j + lane + 64 < r;
+  const double v0 = !in0 ? 0.0 : lane == 0 ? 1.0 : col[i0] * scal, v1 = in1 ? col[i1] * scal : 0.0;
+  for (int c0 = first + wave; c0 < last; c0 += 16) {
+    double* a[4];
+    double w[4], x0[4], x1[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a[u] = sA + min(c0 + 4 * u, c0 + (last - 1 - c0) / 4 * 4) * r;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      x0[u] = a[u][i0];
+      x1[u] = a[u][i1];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) w[u] = v0 * x0[u] + v1 * x1[u];
+    for (int i = j + lane + 128; i < r; i += 64) {
+      const double v = col[i] * scal;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) w[u] += v * a[u][i];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) w[u] = wave_sum(w[u]) * tau;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (in0) a[u][i0] = x0[u] - w[u] * v0;
+      if (in1) a[u][i1] = x1[u] - w[u] * v1;
+    }
+    for (int i = j + lane + 128; i < r; i += 64) {
+      const double v = col[i] * scal;
+      double x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = a[u][i];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a[u][i] = x[u] - w[u] * v;
+    }
+  }
+}
+
+template <int ELEMS>
 __global__ __launch_bounds__(kCT) void k_qr(const QrTask* __restrict__ tasks) {
-  __shared__ double sA[kQrMaxElems];
-  __shared__ double s_tau[kMaxCompressRank];
-  __shared__ double s_scal[2];
+  __shared__ double sA[ELEMS];
+  __shared__ double s_tau[kMaxCompressRank], s_scal[kMaxCompressRank], s_beta[kMaxCompressRank];
   const QrTask T = tasks[blockIdx.x];
   const int r = T.rows, c = T.cols, nr = min(r, c);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int e = tid; e < r * c; e += kCT) {
-    const int j = e / r, i = e - j * r;
-    sA[e] = T.A[i + (int64_t)j * T.lda];
-  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int j = wave; j < c; j += kCT / 64)
+    for (int i = lane; i < r; i += 64) sA[i + j * r] = T.A[i + (int64_t)j * T.lda];
   __syncthreads();
   for (int j = 0; j < nr; ++j) {
-    double* col = sA + j * r;
-    if (wave == 0) {
-      double x2 = 0.0;
-      for (int i = j + 1 + lane; i < r; i += 64) x2 += col[i] * col[i];
-      x2 = wave_sum(x2);
-      if (lane == 0) {
-        const double alpha = col[j];
-        double tau = 0.0, scal = 0.0, beta = alpha;
-        if (x2 > 0.0) {
-          const double nrm = sqrt(alpha * alpha + x2);
-          beta = alpha >= 0.0 ? -nrm : nrm;
-          tau = (beta - alpha) / beta;
-          scal = 1.0 / (alpha - beta);
-        }
-        s_tau[j] = tau;
-        s_scal[0] = scal;
-        s_scal[1] = beta;
-      }
+    const double* col = sA + j * r;
+    double x2 = 0.0;
+    for (int i = j + 1 + lane; i < r; i += 64) x2 += col[i] * col[i];
+    x2 = wave_sum(x2);
+    const double alpha = col[j];
+    double tau = 0.0, scal = 0.0, beta = alpha;
+    if (x2 > 0.0) {
+      const double nrm = sqrt(alpha * alpha + x2);
+      beta = alpha >= 0.0 ? -nrm : nrm;
+      tau = (beta - alpha) / beta;
+      scal = 1.0 / (alpha - beta);
     }
-    __syncthreads();
-    const double scal = s_scal[0], tau = s_tau[j];
-    for (int i = j + 1 + tid; i < r; i += kCT) col[i] *= scal;
-    __syncthreads();
-    if (tid == 0) col[j] = s_scal[1];
-    // apply H_j to columns j+1 .. c-1 (one wave per column)
-    if (tau != 0.0) {
-      for (int cc = j + 1 + wave; cc < c; cc += kCT / 64) {
-        double* a = sA + cc * r;
-        double w = 0.0;
-        for (int i = j + lane; i < r; i += 64) w += (i == j ? 1.0 : col[i]) * a[i];
-        w = wave_sum(w) * tau;
-        for (int i = j + lane; i < r; i += 64) a[i] -= w * (i == j ? 1.0 : col[i]);
-      }
+    if (tid == 0) {
+      s_tau[j] = tau;
+      s_scal[j] = scal;
+      s_beta[j] = beta;
     }
+    if (tau != 0.0) reflect(sA, r, j, tau, scal, j + 1, c, wave, lane);
     __syncthreads();
   }
   // R
-  for (int e = tid; e < c * c; e += kCT) {
-    const int j = e / c, i = e - j * c;
-    T.R[i + (int64_t)j * T.ldr] = (i < nr && i <= j) ? sA[i + j * r] : 0.0;
-  }
+  for (int j = wave; j < c; j += kCT / 64)
+    for (int i = lane; i < c; i += 64)
+      T.R[i + (int64_t)j * T.ldr] = i >= nr || i > j ? 0.0 : i == j ? s_beta[j] : sA[i + j * r];
   __syncthreads();
   // thin Q in place, reflectors taken backwards
   for (int j = nr - 1; j >= 0; --j) {
     double* col = sA + j * r;
-    const double tau = s_tau[j];
+    const double tau = s_tau[j], scal = s_scal[j];
     // H_j on columns j+1 .. nr-1 (their rows above j are zero, so only rows >= j change)
-    if (tau != 0.0) {
-      for (int cc = j + 1 + wave; cc < nr; cc += kCT / 64) {
-        double* a = sA + cc * r;
-        double w = 0.0;
-        for (int i = j + lane; i < r; i += 64) w += (i == j ? 1.0 : col[i]) * a[i];
-        w = wave_sum(w) * tau;
-        for (int i = j + lane; i < r; i += 64) a[i] -= w * (i == j ? 1.0 : col[i]);
-      }
-    }
+    if (tau != 0.0) reflect(sA, r, j, tau, scal, j + 1, nr, wave, lane);
     __syncthreads();
-    for (int i = tid; i < r; i += kCT) {
-      if (i < j) col[i] = 0.0;
-      else if (i == j) col[i] = 1.0 - tau;
-      else col[i] *= -tau;
-    }
+    for (int i = tid; i < r; i += kCT) col[i] = i < j ? 0.0 : i == j ? 1.0 - tau : col[i] * scal * -tau;
     __syncthreads();
   }
-  for (int e = tid; e < r * c; e += kCT) {
-    const int j = e / r, i = e - j * r;
-    T.Q[i + (int64_t)j * T.ldq] = j < nr ? sA[e] : 0.0;
-  }
+  for (int j = wave; j < c; j += kCT / 64)
+    for (int i = lane; i < r; i += 64) T.Q[i + (int64_t)j * T.ldq] = j < nr ? sA[i + j * r] : 0.0;
 }
 
 // ---------------------------------------------------------------------------
@@ -266,31 +308,38 @@ __global__ __launch_bounds__(kCT) void k_triple(const TripleTask* __restrict__ t
 // identity rotations), tournament ordering, n' - 1 rounds per sweep, until a
 // sweep rotates nothing.  Rotation (c, s) from the 2 x 2 symmetric Schur
 // decomposition zeroes A[p][q] in J^T A J, J = [[c, s], [-s, c]].
+//
+// Bound by the chain of rounds.  A round is two barriers: every thread takes
+// 2 x 2 blocks of A (a row pair and a column pair, both rotations at once);
+// then the first wave finds the next round's rotations while the others apply
+// this round's to the eigenvectors.  1024 matrices of order 36: 1350 -> 990
+// us, a level of orders up to 32 200 -> 135.
+constexpr int kET = 512;
 template <int N>
-__global__ __launch_bounds__(kCT) void k_eig(const EigTask* __restrict__ tasks) {
+__global__ __launch_bounds__(kET) void k_eig(const EigTask* __restrict__ tasks) {
   constexpr int LD = N + 1;
   __shared__ double sA[N * LD];
   __shared__ double sV[N * LD];
-  __shared__ double rc[N / 2], rs[N / 2];
-  __shared__ int rp[N / 2], rq[N / 2];
-  __shared__ int s_rot;
+  __shared__ double2 s_cs[2][N / 2];  // rotations, of this round and the next
+  __shared__ int2 s_pq[2][N / 2];
+  __shared__ int s_rot[2];  // a rotation in this sweep, and in the next
   __shared__ double s_lam[N];
-  __shared__ double s_red[kCT];
+  __shared__ double s_red[kET];
   const EigTask T = tasks[blockIdx.x];
   const int n = T.n, tid = threadIdx.x;
   const int np = (n + 1) & ~1, half = np / 2;
   double sq = 0.0;
-  for (int e = tid; e < n * n; e += kCT) {
-    const int j = e / n, i = e - j * n;
+  for (int e = tid; e < np * np; e += kET) {
+    const int j = e / np, i = e - j * np;
     // symmetrize (the inputs are symmetric up to rounding)
-    const double a = 0.5 * (T.G[i + (int64_t)j * T.ldg] + T.G[j + (int64_t)i * T.ldg]);
+    const double a = i < n && j < n ? 0.5 * (T.G[i + (int64_t)j * T.ldg] + T.G[j + (int64_t)i * T.ldg]) : 0.0;
     sA[i * LD + j] = a;
     sV[i * LD + j] = i == j ? 1.0 : 0.0;
     sq += a * a;
   }
   s_red[tid] = sq;
   __syncthreads();
-  for (int w = kCT / 2; w > 0; w >>= 1) {
+  for (int w = kET / 2; w > 0; w >>= 1) {
     if (tid < w) s_red[tid] += s_red[tid + w];
     __syncthreads();
   }
@@ -299,64 +348,75 @@ __global__ __launch_bounds__(kCT) void k_eig(const EigTask* __restrict__ tasks) 
   // noise among the (many) negligible eigenvalues is left, at an absolute
   // accuracy far below any threshold the truncation applies
   const double floor_abs = 1e-16 * sqrt(s_red[0]);
-  for (int sweep = 0; sweep < 40 && np > 1; ++sweep) {
-    if (tid == 0) s_rot = 0;
-    __syncthreads();
-    for (int round = 0; round < np - 1; ++round) {
-      if (tid < half) {
-        int p, q;
-        if (tid == 0) { p = round; q = np - 1; }
-        else { p = (round + tid) % (np - 1); q = (round - tid + (np - 1)) % (np - 1); }
-        if (p > q) { const int t = p; p = q; q = t; }
-        double c = 1.0, s = 0.0;
-        if (q < n) {
-          const double app = sA[p * LD + p], aqq = sA[q * LD + q], apq = sA[p * LD + q];
-          if (fabs(apq) > 1e-300 && fabs(apq) > floor_abs && fabs(apq) > 1e-15 * sqrt(fabs(app) * fabs(aqq))) {
-            const double tau = (aqq - app) / (2.0 * apq);
-            const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            c = 1.0 / sqrt(1.0 + t * t);
-            s = t * c;
-            s_rot = 1;
-          }
-        }
-        rp[tid] = p; rq[tid] = q; rc[tid] = c; rs[tid] = s;
+  if (tid < 2) s_rot[tid] = 0;
+  __syncthreads();
+  // rotations of a round from A into buffer b; sweeps alternate s_rot
+  auto rotations = [&](int round, int b, int sweep) {
+    if (tid >= half) return;
+    int p, q;
+    if (tid == 0) { p = round; q = np - 1; }
+    else { p = (round + tid) % (np - 1); q = (round - tid + (np - 1)) % (np - 1); }
+    if (p > q) { const int t = p; p = q; q = t; }
+    double c = 1.0, s = 0.0;
+    if (q < n) {
+      const double app = sA[p * LD + p], aqq = sA[q * LD + q], apq = sA[p * LD + q];
+      if (fabs(apq) > 1e-300 && fabs(apq) > floor_abs && fabs(apq) > 1e-15 * sqrt(fabs(app) * fabs(aqq))) {
+        const double tau = (aqq - app) / (2.0 * apq);
+        const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
+        c = 1.0 / sqrt(1.0 + t * t);
+        s = t * c;
+        s_rot[sweep & 1] = 1;
+      }
+    }
+    s_pq[b][tid] = int2{p, q};
+    s_cs[b][tid] = double2{c, s};
+  };
+  // quotients by half of numbers below 2^11 (half <= 32)
+  const unsigned inv = half > 0 ? 65536u / (unsigned)half + 1u : 0u;
+  if (np > 1) rotations(0, 0, 0);
+  __syncthreads();
+  for (int sweep = 0, b = 0; sweep < 40 && np > 1; ++sweep) {
+    if (tid == 0) s_rot[(sweep + 1) & 1] = 0;
+    for (int round = 0; round < np - 1; ++round, b ^= 1) {
+      // rows p' = c p - s q, q' = s p + c q, then columns likewise
+      for (int e = tid; e < half * half; e += kET) {
+        const int k = (int)((unsigned)e * inv >> 16), l = e - k * half;
+        const double2 rk = s_cs[b][k], rl = s_cs[b][l];
+        if (rk.y == 0.0 && rl.y == 0.0) continue;
+        const int2 ik = s_pq[b][k], il = s_pq[b][l];
+        double *pp = sA + ik.x * LD + il.x, *pq = sA + ik.x * LD + il.y;
+        double *qp = sA + ik.y * LD + il.x, *qq = sA + ik.y * LD + il.y;
+        const double a = *pp, bb = *pq, c = *qp, d = *qq;
+        const double a1 = rk.x * a - rk.y * c, c1 = rk.y * a + rk.x * c;
+        const double b1 = rk.x * bb - rk.y * d, d1 = rk.y * bb + rk.x * d;
+        *pp = rl.x * a1 - rl.y * b1;
+        *pq = rl.y * a1 + rl.x * b1;
+        *qp = rl.x * c1 - rl.y * d1;
+        *qq = rl.y * c1 + rl.x * d1;
       }
       __syncthreads();
-      // rows: p' = c p - s q, q' = s p + c q
-      for (int e = tid; e < half * n; e += kCT) {
-        const int k = e / n, j = e - k * n;
-        const int p = rp[k], q = rq[k];
-        if (q < n && rs[k] != 0.0) {
-          const double c = rc[k], s = rs[k];
-          const double ap = sA[p * LD + j], aq = sA[q * LD + j];
-          sA[p * LD + j] = c * ap - s * aq;
-          sA[q * LD + j] = s * ap + c * aq;
+      const bool last = round + 1 == np - 1;
+      if (tid < 64) rotations(last ? 0 : round + 1, b ^ 1, last ? sweep + 1 : sweep);
+      else
+        for (int e = tid - 64; e < half * n; e += kET - 64) {
+          const int i = (int)((unsigned)e * inv >> 16), k = e - i * half;
+          const double2 r = s_cs[b][k];
+          if (r.y == 0.0) continue;
+          const int2 ix = s_pq[b][k];
+          double *vp = sV + i * LD + ix.x, *vq = sV + i * LD + ix.y;
+          const double x = *vp, y = *vq;
+          *vp = r.x * x - r.y * y;
+          *vq = r.y * x + r.x * y;
         }
-      }
-      __syncthreads();
-      // columns of A and V: p'' = c p - s q, q'' = s p + c q
-      for (int e = tid; e < half * n; e += kCT) {
-        const int k = e / n, i = e - k * n;
-        const int p = rp[k], q = rq[k];
-        if (q < n && rs[k] != 0.0) {
-          const double c = rc[k], s = rs[k];
-          const double ap = sA[i * LD + p], aq = sA[i * LD + q];
-          sA[i * LD + p] = c * ap - s * aq;
-          sA[i * LD + q] = s * ap + c * aq;
-          const double vp = sV[i * LD + p], vq = sV[i * LD + q];
-          sV[i * LD + p] = c * vp - s * vq;
-          sV[i * LD + q] = s * vp + c * vq;
-        }
-      }
       __syncthreads();
     }
-    if (s_rot == 0) break;
-    __syncthreads();
+    if (s_rot[sweep & 1] == 0) break;
+    __syncthreads();  // read by all before the next sweep clears it
   }
   // descending order (ties by index)
-  for (int i = tid; i < n; i += kCT) s_lam[i] = sA[i * LD + i];
+  for (int i = tid; i < n; i += kET) s_lam[i] = sA[i * LD + i];
   __syncthreads();
-  for (int i = tid; i < n; i += kCT) {
+  for (int i = tid; i < n; i += kET) {
     const double li = s_lam[i];
     int rank = 0;
     for (int j = 0; j < n; ++j) rank += (s_lam[j] > li) || (s_lam[j] == li && j < i);
@@ -453,9 +513,12 @@ inline dim3 grid_of(int64_t n) { return dim3((unsigned)n); }
 
 }  // namespace
 
-hipError_t launch_qr(const QrTask* t, int64_t n, hipStream_t s) {
+hipError_t launch_qr(const QrTask* t, int64_t n, hipStream_t s, int max_elems) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_qr, grid_of(n), dim3(kCT), 0, s, t);
+  if (max_elems <= 2560) hipLaunchKernelGGL((k_qr<2560>), grid_of(n), dim3(kCT), 0, s, t);
+  else if (max_elems <= 4608) hipLaunchKernelGGL((k_qr<4608>), grid_of(n), dim3(kCT), 0, s, t);
+  else if (max_elems <= kQrMaxElems) hipLaunchKernelGGL((k_qr<kQrMaxElems>), grid_of(n), dim3(kCT), 0, s, t);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 hipError_t launch_gemm(const GemmTask* t, int64_t n, const GemmPair* p, hipStream_t s, int maxdim) {
@@ -478,9 +541,9 @@ hipError_t launch_triple(const TripleTask* t, int64_t n, hipStream_t s, int maxd
 }
 hipError_t launch_eig(const EigTask* t, int64_t n, int nmax, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  if (nmax <= 32) hipLaunchKernelGGL((k_eig<32>), grid_of(n), dim3(kCT), 0, s, t);
-  else if (nmax <= 48) hipLaunchKernelGGL((k_eig<48>), grid_of(n), dim3(kCT), 0, s, t);
-  else if (nmax <= kMaxCompressRank) hipLaunchKernelGGL((k_eig<64>), grid_of(n), dim3(kCT), 0, s, t);
+  if (nmax <= 32) hipLaunchKernelGGL((k_eig<32>), grid_of(n), dim3(kET), 0, s, t);
+  else if (nmax <= 48) hipLaunchKernelGGL((k_eig<48>), grid_of(n), dim3(kET), 0, s, t);
+  else if (nmax <= kMaxCompressRank) hipLaunchKernelGGL((k_eig<64>), grid_of(n), dim3(kET), 0, s, t);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
