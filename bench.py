@@ -220,6 +220,8 @@ def launches_per_product(g) -> int:
     if any(line.startswith("input ") for line in g.plan_info().splitlines()):
         return 2 + sum(1 for line in g.plan_info().splitlines() if line.startswith("couple "))
     names = ("up ", "couple ", "down ", "dense1 ", "dense2 ", "out ")
+    if any(line.startswith("fp64: streaming sweeps per level") for line in g.plan_info().splitlines()):
+        names = ("level_up ", "couple ", "level_down ", "dense1 ", "dense2 ", "level_out ")
     return 1 + sum(1 for line in g.plan_info().splitlines() if line.startswith(names) and "skipped" not in line)
 
 

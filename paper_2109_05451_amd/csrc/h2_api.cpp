@@ -334,6 +334,9 @@ void each_launch(Plan& p, F f) {
   f(p.outc);
 }
 
+// Operators smaller than this are loaded without a look at the free memory.
+constexpr int64_t kCheckMemory = int64_t{1} << 30;
+
 // Build plans and upload; the handle's device is current.
 int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* d_dense) {
   const int64_t q = P.q, n = P.n;
@@ -454,8 +457,23 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
       compose_sweeps(lay, B, true, cn.ntrans, true, &ct);
       if (!composed_fits(ct)) compose_sweeps(lay, B, true, cn.ntrans, false, &ct);
     }
+    // composed rows are extra memory (a few per cent of a large operator): not
+    // taken where the operator then no longer fits
+    const int64_t need = P.off_end - P.off_U + 8 * (h->shared ? cn : ct).ntrans;
+    size_t free_b = 0, total_b = 0;
+    if (need > kCheckMemory && hipMemGetInfo(&free_b, &total_b) == hipSuccess && need + need / 16 > (int64_t)free_b) {
+      compose_sweeps(lay, B, false, ntrans, false, &cn);
+      if (!h->shared) compose_sweeps(lay, B, true, cn.ntrans, false, &ct);
+    }
     int rc;
-    if ((rc = add_composed(h, cn, h->planN)) || (rc = add_composed(h, h->shared ? cn : ct, h->planT))) return rc;
+    if ((rc = add_composed(h, cn, h->planN)) != H2_OK) return rc;
+    if (h->shared) {
+      h->planT.upc = h->planN.upc;
+      h->planT.downc = h->planN.downc;
+      h->planT.outc = h->planN.outc;
+    } else if ((rc = add_composed(h, ct, h->planT)) != H2_OK) {
+      return rc;
+    }
   }
   const int64_t ntrans_all = h->shared ? cn.ntrans : ct.ntrans;
   {
@@ -1028,6 +1046,14 @@ int sched_of(const h2_op_s* h, int set, bool mfma) {
   return set != kAutoSched ? set : h->nleaves < (mfma ? 8192 : 2048) ? 2 : 0;
 }
 
+// From this many leaves on the streaming path of op 'N' runs its sweeps level by
+// level: half the dense rows cover each of them, and a shorter chain only moves
+// the coupling rows beside the dense ones.  One vector, composed against per
+// level in us: 262 144 points (4096 leaves) 538 / 562; 8192 and 16 384 leaves:
+// 524 288 points 1134 / 1065, 600 000 1418 / 1428, 700 000 1754 / 1827, 2^20
+// 1947 / 1944 and, with eta 0.9, 1483 / 1420.
+constexpr int64_t kComposedStream = 8192;
+
 // One pass of the product: nv <= kPassVectors vectors on the streaming path
 // (nvp == 0), or nv <= kPassVectorsMfma vectors padded to nvp on the MFMA path.
 int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const double* X, int64_t ldx, int nv,
@@ -1038,7 +1064,7 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
   const int cm = (!trans && nvp > 0) ? h->couple_mode[pidx] : 0;
   const int dm = (!trans && nvp > 0) ? h->dense_mode[pidx] : 0;
   // FP64: the sweeps in composed stages
-  const bool comp = prec == H2_PREC_FP64;
+  const bool comp = prec == H2_PREC_FP64 && (nvp > 0 || trans || h->nleaves < kComposedStream);
   const std::vector<Launch>& up = comp ? plan.upc : plan.up;
   const std::vector<Launch>& down = comp ? plan.downc : plan.down;
   const Launch& outl = comp ? plan.outc : plan.out;
@@ -1850,6 +1876,7 @@ int h2_plan_info(h2_handle h, char* buf, size_t cap, size_t* needed) {
                   h->sweep_ms[p][0], h->sweep_ms[p][1]);
     t += line;
   }
+  if (h->nleaves >= kComposedStream) t += "fp64: streaming sweeps per level\n";
   for (int p = 0; p < 3; ++p) {
     std::snprintf(line, sizeof line, "%s: dense schedule %d (tuned products %.3f / %.3f / %.3f / %.3f ms)\n",
                   pn[p], sched_of(h, h->sched[p], true), h->sched_ms[p][0], h->sched_ms[p][1], h->sched_ms[p][2], h->sched_ms[p][3]);

@@ -56,10 +56,12 @@ class Arena {
     for (void* p : ptrs_) (void)hipFree(p);
   }
   // Room for `bytes` of later allocations in one device allocation (each one
-  // and its release cost tens of microseconds); where it does not fit, they are
-  // made one by one.
+  // and its release cost tens of microseconds); where it would take over half of
+  // the free memory, they are made one by one.
   void reserve(size_t bytes) {
     void* p = nullptr;
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || bytes > free_b / 2) return;
     if (hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
       return;
