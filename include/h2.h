@@ -146,8 +146,9 @@ int h2_validate(const void* buf, size_t len);
  * kernel.  Results are deterministic (no floating-point atomics).  A
  * handle's workspace is shared: calls on one handle must not run
  * concurrently on different streams.  The workspace is allocated on the
- * first call unless h2_reserve allocated it first; vectors are processed
- * in passes of up to 4.
+ * first call unless h2_reserve allocated it first; up to 4 vectors are one
+ * pass of the streaming kernels, more go in passes of up to 64 on the
+ * matrix cores (op 'T' in FP64 too; in FP32 in passes of 4).
  * Errors: H2_EINVAL, H2_ENOMEM, H2_EHIP. */
 int h2_gemv(h2_handle h, char op, double alpha, const double* X, int64_t ldx, int64_t nv,
             double beta, double* Y, int64_t ldy, void* stream);
@@ -217,7 +218,7 @@ int h2_reserve(h2_handle h, int64_t nv_max);
  * HIP events on `stream` (three runs, the first discarded) on zeroed
  * workspace buffers, and the fastest is kept for later calls in that
  * precision (the dense rows, always FP64, keep theirs in the FP64 entry);
- * then the fused sweeps are timed against the tuned per-level sweeps and the
+ * then (FP32) the fused sweeps are timed against the tuned per-level sweeps and the
  * faster form is kept (h2_set_sweeps), and the four schedules of
  * h2_set_schedule are timed on whole products (zeroed input) and the
  * fastest is kept (a later schedule in the list only when it is at least 1%
@@ -290,8 +291,10 @@ int h2_ranks(h2_handle h, int64_t* krow, int64_t* kcol, int64_t cap);
  * 64 outputs, any pass width), 10 the same with one wave per 16-vector tile
  * (passes of 32 or 64 vectors), 11 a second form of 9 (two waves per row at 64
  * vectors, half the columns per load group at 16 and 32), 12 as 10;
- * grid = workgroups (0 = one per row); xcd != 0 for XCD-aware row ranges; tree_order != 0 for tree-ordered
- * coupling and dense rows.  Results do not change (same summation order).  For
+ * grid = workgroups (0 = one per row); xcd != 0 for XCD-aware row ranges;
+ * tree_order != 0 for tree-ordered coupling and dense rows.  The composed FP64
+ * sweep rows, and the dense rows of operators of fewer than 8192 leaves, have
+ * one kernel whatever kc.  Results do not change (same summation order).  For
  * reproducible timing and for tests.  Errors: H2_EINVAL. */
 int h2_tune_set(h2_handle h, int prec, int kc, int64_t grid, int xcd, int tree_order);
 
@@ -318,16 +321,18 @@ int h2_set_dense_grid(h2_handle h, int64_t workgroups);
  *      upper downsweep; the last downsweep level waits for them (not with
  *      the fused sweeps, nor for FP32 passes of 64 vectors, which take
  *      schedule 2 instead)
- * Results are bitwise the same; h2_tune keeps the fastest.  Synchronizes the
- * device.  Errors: H2_EINVAL. */
+ * Until set or tuned: 2 on operators of fewer than 8192 leaves (multi-vector)
+ * or 2048 (streaming), else 0.  Results are bitwise the same; h2_tune keeps the
+ * fastest.  Synchronizes the device.  Errors: H2_EINVAL. */
 int h2_set_schedule(h2_handle h, int prec, int schedule);
 
-/* How the multi-vector path (op 'N', 64-vector passes or fewer, FP64 and
- * FP32) runs the upsweep, the downsweep and the leaf expansion: fused != 0
- * in a few launches in which each workgroup runs several levels of one
- * subtree (operators whose rows have at most 64 outputs), 0 one launch per
- * level (the default).  Results are bitwise the same; h2_tune keeps the
- * faster.
+/* How the multi-vector path (op 'N', 64-vector passes or fewer) runs the
+ * FP32 upsweep, downsweep and leaf expansion: fused != 0 in a few launches in
+ * which each workgroup runs several levels of one subtree (operators whose
+ * rows have at most 64 outputs), 0 one launch per level (the default).
+ * Results are bitwise the same; h2_tune keeps the faster.  FP64 is accepted
+ * and changes nothing: its sweeps run in composed stages, several transfer
+ * levels per launch.
  * Errors: H2_EINVAL (null handle, precision other than FP64 or FP32),
  * H2_EUNSUPPORTED (fused asked for, but the operator has longer rows). */
 int h2_set_sweeps(h2_handle h, int prec, int fused);
