@@ -188,8 +188,9 @@ int h2_gemv_noalloc(h2_handle h, char op, double alpha, const double* X, int64_t
  * a non-null stream) captures its launch sequence into a HIP graph, and
  * later calls with the same arguments replay it with one launch (X is read
  * afresh at every replay).  Up to 8 graphs are kept per handle, the least
- * recently used dropped first; retuning (h2_tune, h2_tune_set,
- * h2_set_sweeps, h2_set_dense_grid) drops them all.  For repeated products on
+ * recently used dropped first; retuning (h2_tune, h2_tune_set, h2_set_schedule,
+ * h2_set_sweeps, h2_set_dense_grid, h2_set_fragment_order) and a call whose
+ * workspace has to grow drop them all.  For repeated products on
  * the same buffers, where launching the sequence costs more than the GPU
  * work (small operators).  Calls on the null stream, or while profiling, are
  * not captured.  No memset nodes are captured.  Disabling drops the graphs.

@@ -700,6 +700,7 @@ int ensure_workspace(h2_op_s* h, int64_t nv) {
   if (h->ws.cap >= want) return H2_OK;
   if (h->ws.cap > 0) {  // grow: the old buffers may still be in use by queued work
     HIP_TRY(hipDeviceSynchronize(), "hipDeviceSynchronize(workspace growth)");
+    drop_graphs(h);  // captured with the old buffers
     h->stats.device_bytes -= ws_bytes(h->ws.n, h->ws.H, h->ws.cap);
     ws_destroy(&h->ws);
   }

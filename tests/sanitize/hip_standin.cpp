@@ -71,7 +71,8 @@ std::set<Event*> g_events;
 std::set<GraphExec*> g_execs;
 std::vector<OpP> g_pending;
 std::map<void*, size_t> g_mem;
-size_t g_used = 0, g_limit = size_t(1) << 34;
+size_t g_used = 0, g_peak = 0, g_limit = size_t(1) << 34;
+bool g_hide_free = false;
 uint64_t g_seed = 1;
 std::map<std::string, int64_t> g_count;
 Stream g_null;
@@ -161,6 +162,7 @@ hipError_t do_malloc(void** p, size_t n) {
   std::memset(q, 0xa5, n);
   g_mem[q] = n;
   g_used += n;
+  g_peak = std::max(g_peak, g_used);
   *p = q;
   return hipSuccess;
 }
@@ -174,7 +176,13 @@ void h2_standin_limit(int64_t free_bytes) {  // free device memory from now on (
   Lock l(g_mu);
   g_limit = free_bytes < 0 ? size_t(1) << 34 : g_used + (size_t)free_bytes;
 }
-int64_t h2_standin_used() { Lock l(g_mu); return (int64_t)g_used; }
+void h2_standin_hide_free(int hide) { Lock l(g_mu); g_hide_free = hide != 0; }  // hipMemGetInfo says that nothing is free
+int64_t h2_standin_peak() {  // largest memory held beyond the present since the last call
+  Lock l(g_mu);
+  const int64_t p = (int64_t)g_peak - (int64_t)g_used;
+  g_peak = g_used;
+  return p;
+}
 int64_t h2_standin_count(const char* name) { Lock l(g_mu); return g_count[name]; }
 int64_t h2_standin_live() { Lock l(g_mu); return (int64_t)(g_streams.size() + g_events.size() + g_execs.size() + g_mem.size()); }
 }
@@ -189,7 +197,7 @@ hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipMemGetInfo(size_t* f, size_t* t) {
   Lock l(g_mu);
-  *f = g_limit - g_used;
+  *f = g_hide_free ? 0 : g_limit - g_used;
   *t = g_limit;
   return hipSuccess;
 }

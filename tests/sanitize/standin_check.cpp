@@ -19,7 +19,8 @@
 extern "C" {
 void h2_standin_seed(uint64_t);
 void h2_standin_limit(int64_t);
-int64_t h2_standin_used();
+void h2_standin_hide_free(int);
+int64_t h2_standin_peak();
 int64_t h2_standin_count(const char*);
 int64_t h2_standin_live();
 // the oracle (oracle/h2_oracle.c)
@@ -179,6 +180,151 @@ void graphs(const std::vector<File>& files, hipStream_t s) {
   }
 }
 
+// A workspace that grows while captured graphs of the smaller one are kept.
+void growth(const std::vector<File>& files, hipStream_t s) {
+  for (const File& f : files) {
+    Pair p(f);
+    OK(h2_graph(p.h, 1));
+    Vec X = random_vec(p.n), Y((size_t)p.n);
+    for (int rep = 0; rep < 2; ++rep) {
+      OK(h2_gemv(p.h, 'N', 1.0, X.data(), p.n, 1, 0.0, Y.data(), p.n, s));
+      (void)hipDeviceSynchronize();
+      p.check(X, Y, Y, 'N', 1, 1.0, 0.0, kTol[0], "one vector");
+      product(p, 'N', 20, 0, s, "growing");
+    }
+  }
+}
+
+// Graphs captured on a stream that the caller has destroyed since.
+void streams(const std::vector<File>& files, hipStream_t s) {
+  Pair p(files[0]);
+  OK(h2_graph(p.h, 1));
+  hipStream_t t = nullptr;
+  (void)hipStreamCreateWithFlags(&t, hipStreamNonBlocking);
+  product(p, 'N', 1, 0, t, "a stream of its own");
+  (void)hipStreamDestroy(t);
+  const Vec X = random_vec(p.n);
+  std::vector<Vec> Y(12, Vec((size_t)p.n));
+  for (Vec& y : Y) OK(h2_gemv(p.h, 'N', 1.0, X.data(), p.n, 1, 0.0, y.data(), p.n, s));
+  (void)hipDeviceSynchronize();
+  for (const Vec& y : Y) p.check(X, y, y, 'N', 1, 1.0, 0.0, kTol[0], "after the stream");
+}
+
+// A batch tuned while a replay of its graph is queued.
+void batch(const std::vector<File>& files, hipStream_t s) {
+  std::vector<const void*> bufs;
+  std::vector<size_t> lens;
+  std::vector<int64_t> nv;
+  for (size_t i = 0; i < files.size(); ++i) {
+    bufs.push_back(files[i].mem.data());
+    lens.push_back((size_t)files[i].len);
+    nv.push_back(i % 2 ? 3 : 33);
+  }
+  h2_batch b = nullptr;
+  OK(h2_batch_load_ex(bufs.data(), lens.data(), (int64_t)bufs.size(), nv.data(), 0, &b));
+  std::vector<Pair*> ops;
+  std::vector<Vec> X, Y;
+  std::vector<h2_batch_item> it;
+  for (size_t i = 0; i < files.size(); ++i) {
+    ops.push_back(new Pair(files[i]));
+    X.push_back(random_vec(ops[i]->n * nv[i]));
+    Y.emplace_back((size_t)(ops[i]->n * nv[i]));
+    it.push_back({X[i].data(), ops[i]->n, Y[i].data(), ops[i]->n, nv[i], 1.0, 0.0});
+  }
+  OK(h2_batch_graph(b, 1));
+  for (int round = 0; round < 2; ++round) {
+    for (int rep = 0; rep < 3; ++rep) OK(h2_batch_gemv(b, it.data(), s));
+    if (round == 0) OK(h2_batch_tune(b, it.data(), s));
+  }
+  (void)hipDeviceSynchronize();
+  for (size_t i = 0; i < files.size(); ++i) {
+    ops[i]->check(X[i], Y[i], Y[i], 'N', nv[i], 1.0, 0.0, kTol[0], "batch");
+    delete ops[i];
+  }
+  OK(h2_batch_free(b));
+}
+
+// The least free memory with which an operator loads is that of the sweeps
+// level by level, not of the composed ones.
+void memory(const std::vector<File>& files, hipStream_t s) {
+  for (const File& f : files) {
+    h2_stats_t full{}, st{};
+    {
+      Pair p(f);
+      OK(h2_stats(p.h, &full));
+    }
+    (void)h2_standin_peak();
+    int64_t lo = 0, hi = 2 * full.device_bytes + (int64_t(1) << 20);  // refused, accepted
+    while (hi - lo > 64) {
+      const int64_t mid = (lo + hi) / 2;
+      h2_handle h = nullptr;
+      h2_standin_limit(mid);
+      const int rc = h2_load_mem(f.mem.data(), (size_t)f.len, 0, &h);
+      if (rc == H2_OK) OK(h2_free(h));
+      else if (rc != H2_ENOMEM) fail("load without memory");
+      (rc == H2_OK ? hi : lo) = mid;
+    }
+    h2_standin_limit(hi);
+    {
+      Pair p(f);
+      h2_standin_limit(-1);
+      OK(h2_stats(p.h, &st));
+      for (char op : {'N', 'T'})
+        for (int64_t nv : {1, 20}) product(p, op, nv, 0, s, "least memory");
+    }
+    if (st.device_bytes >= full.device_bytes) fail("the composed sweeps are kept where memory is short");
+  }
+}
+
+// Recompression needs no more memory than its arrays one by one.
+void compress_memory(const std::vector<File>& files, hipStream_t s) {
+  for (const File& f : files) {
+    h2_handle h = nullptr, c = nullptr;
+    OK(h2_load_mem(f.mem.data(), (size_t)f.len, 0, &h));
+    (void)h2_standin_peak();
+    h2_standin_hide_free(1);
+    OK(h2_compress(h, 1e-3, &c, nullptr, s));
+    h2_standin_hide_free(0);
+    OK(h2_free(c));
+    const int64_t peak = h2_standin_peak();
+    h2_standin_limit(peak);
+    OK(h2_compress(h, 1e-3, &c, nullptr, s));
+    h2_standin_limit(-1);
+    OK(h2_free(c));
+    OK(h2_free(h));
+  }
+}
+
+// FP32 passes of 64 vectors convert x^ only for launches that read the copy.
+void fp32(const std::vector<File>& files, hipStream_t s) {
+  bool split = false;
+  for (const File& f : files) {
+    Pair p(f);
+    OK(h2_prepare(p.h, H2_PREC_FP32));
+    auto run = [&](const char* what, int64_t* conv, int64_t* reads) {
+      const int64_t c = h2_standin_count("to_f32"), r = h2_standin_count("reads_x32"), w = h2_standin_count("wave_rows");
+      product(p, 'N', 64, 1, s, what);
+      *conv = h2_standin_count("to_f32") - c;
+      *reads = h2_standin_count("reads_x32") - r;
+      return h2_standin_count("wave_rows") - w;
+    };
+    int64_t conv, reads;
+    for (int sched : {0, 2, 3}) {
+      OK(h2_set_schedule(p.h, H2_PREC_FP32, sched));
+      const int64_t waves = run("untuned", &conv, &reads);
+      if ((conv > 0) != (reads > 0)) fail("a conversion of x^ that nothing reads");
+      if (sched == 3) {
+        OK(h2_set_schedule(p.h, H2_PREC_FP32, 2));
+        split = split || run("schedule 2", &conv, &reads) < waves;
+      }
+    }
+    OK(h2_tune_set(p.h, H2_PREC_FP32, 64, 0, 0, 0));
+    run("staged", &conv, &reads);
+    if (conv != 1 || reads == 0) fail("the staged kernel without the copy of x^");
+  }
+  if (!split) fail("schedule 3 taken as 2 everywhere");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -191,6 +337,12 @@ int main(int argc, char** argv) {
   const int64_t live = h2_standin_live();
   if (name == "products") products(files, s);
   else if (name == "graphs") graphs(files, s);
+  else if (name == "growth") growth(files, s);
+  else if (name == "streams") streams(files, s);
+  else if (name == "batch") batch(files, s);
+  else if (name == "memory") memory(files, s);
+  else if (name == "compress_memory") compress_memory(files, s);
+  else if (name == "fp32") fp32(files, s);
   else return 2;
   if (h2_standin_live() != live) fail("streams, events, graphs or memory left behind");
   (void)hipStreamDestroy(s);

@@ -77,3 +77,7 @@ def test_products(exe, tmp_path):
 
 def test_graph_replays(exe, tmp_path):
     run(exe, tmp_path, "graphs", reps(range(1, 8, 3)))
+
+
+def test_growing_workspace_drops_graphs(exe, tmp_path):
+    run(exe, tmp_path, "growth", reps(range(2, 5)))
