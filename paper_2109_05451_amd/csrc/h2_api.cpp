@@ -1503,7 +1503,9 @@ int h2_gemv_ex(h2_handle h, char op, double alpha, const double* X, int64_t ldx,
       size_t lru = 0;
       for (size_t i = 1; i < h->graphs.size(); ++i)
         if (h->graphs[i].last_use < h->graphs[lru].last_use) lru = i;
-      HIP_TRY(hipStreamSynchronize(h->graphs[lru].key.s), "hipStreamSynchronize(graph)");
+      // its last replay must be over; a stream other than this call's may have been destroyed since
+      if (h->graphs[lru].key.s == s) HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize(graph)");
+      else HIP_TRY(hipDeviceSynchronize(), "hipDeviceSynchronize(graph)");
       (void)hipGraphExecDestroy(h->graphs[lru].exec);
       h->graphs.erase(h->graphs.begin() + (long)lru);
     }

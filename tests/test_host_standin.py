@@ -81,3 +81,7 @@ def test_graph_replays(exe, tmp_path):
 
 def test_growing_workspace_drops_graphs(exe, tmp_path):
     run(exe, tmp_path, "growth", reps(range(2, 5)))
+
+
+def test_graphs_of_a_destroyed_stream(exe, tmp_path):
+    run(exe, tmp_path, "streams", reps(range(2, 3)))
