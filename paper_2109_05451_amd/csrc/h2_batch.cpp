@@ -538,6 +538,7 @@ int h2_batch_tune(h2_batch b, const h2_batch_item* items, void* stream) {
   DevGuard guard(b->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool graph_was = b->use_graph;
+  HIP_TRYB(hipDeviceSynchronize(), "hipDeviceSynchronize");  // a replay of the graph may be queued
   b->use_graph = false;
   if (b->graph) { (void)hipGraphExecDestroy(b->graph); b->graph = nullptr; }
   int rc = h2_batch_gemv(b, items, stream);  // fills the workspace with this call's data

@@ -85,3 +85,7 @@ def test_growing_workspace_drops_graphs(exe, tmp_path):
 
 def test_graphs_of_a_destroyed_stream(exe, tmp_path):
     run(exe, tmp_path, "streams", reps(range(2, 3)))
+
+
+def test_batch_tuned_while_a_replay_is_queued(exe, tmp_path):
+    run(exe, tmp_path, "batch", reps()[:-1])
