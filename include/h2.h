@@ -320,8 +320,8 @@ int h2_set_dense_grid(h2_handle h, int64_t workgroups);
  *      (they need only the leaf products of the upsweep) on a third stream
  *      beside the upper upsweep, the other levels' coupling rows and the
  *      upper downsweep; the last downsweep level waits for them (not with
- *      the fused sweeps, nor for FP32 passes of 64 vectors, which take
- *      schedule 2 instead)
+ *      the fused sweeps, nor for FP32 passes of 64 vectors whose coupling rows
+ *      run the LDS-staged kernel, which take schedule 2 instead)
  * Until set or tuned: 2 on operators of fewer than 8192 leaves (multi-vector)
  * or 2048 (streaming), else 0.  Results are bitwise the same; h2_tune keeps the
  * fastest.  Synchronizes the device.  Errors: H2_EINVAL. */

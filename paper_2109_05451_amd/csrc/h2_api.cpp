@@ -1030,6 +1030,17 @@ int run_tree(h2_op_s* h, const Workspace& w, const std::vector<TreeGroup>& group
   return H2_OK;
 }
 
+// Whether one of these FP32 launches runs the LDS-staged kernel, the only one
+// that reads the FP32 copy of x^ (run_launch's choice).  Where none does, the
+// copy (a pass over H * 64 values) is not made.
+bool any_staged(const std::vector<Launch>& v, int nvp) {
+  for (const Launch& L : v) {
+    const int kc = L.kcp[H2_PREC_FP32] == kAutoForm ? auto_form(nvp, L.row_count, L.max_rows).kc : L.kcp[H2_PREC_FP32];
+    if ((kc != kWaveRows && kc != kWaveTiles) || L.max_rows > 64) return true;
+  }
+  return false;
+}
+
 // Whether a multi-vector pass runs the fused sweeps (FP32: FP64 has the composed stages instead).
 bool use_tree(const h2_op_s* h, const Workspace& w, bool trans, int nvp, int prec) {
   const int pidx = prec == H2_PREC_FP32 ? 1 : prec == H2_PREC_BF16 ? 2 : 0;
@@ -1115,12 +1126,14 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
                      dense1[0].kind == dense2[0].kind &&
                      dense1[0].row_begin + dense1[0].row_count == dense2[0].row_begin;
   const bool fused = use_tree(h, w, trans, nvp, prec);
-  // FP32 at 64 vectors: the coupling launches gather x^ from an FP32 copy
-  const bool x32 = prec == H2_PREC_FP32 && nvp == kPassVectorsMfma && w.xh32;
+  // FP32 at 64 vectors: the LDS-staged coupling launches gather x^ from an FP32 copy
+  const bool may32 = prec == H2_PREC_FP32 && nvp == kPassVectorsMfma && w.xh32;
   // (a workspace without the third stream, such as the no-allocation
   // product's views, takes schedule 2's order instead)
-  const bool split = sched == 3 && !fused && !x32 && !down.empty() && !plan.couple_deep.empty() && !up.empty() &&
-                     w.side2 && w.ev_deep && w.ev_deep_done;
+  const bool split = sched == 3 && !fused && !down.empty() && !plan.couple_deep.empty() && !up.empty() && w.side2 &&
+                     w.ev_deep && w.ev_deep_done &&
+                     !(may32 && (any_staged(plan.couple_deep, nvp) || any_staged(plan.couple_rest, nvp)));
+  const bool x32 = may32 && !split && any_staged(couple, nvp);
   // op 'T' of a small operator, one stage each way: its few launches all on the
   // caller's stream (the events of a side stream cost more than it overlaps)
   const bool inl = trans && nvp == 0 && comp && up.size() == 1 && down.empty();

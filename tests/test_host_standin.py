@@ -89,3 +89,7 @@ def test_graphs_of_a_destroyed_stream(exe, tmp_path):
 
 def test_batch_tuned_while_a_replay_is_queued(exe, tmp_path):
     run(exe, tmp_path, "batch", reps()[:-1])
+
+
+def test_fp32_input_copy_only_where_read(exe, tmp_path):
+    run(exe, tmp_path, "fp32", reps()[:-1])
