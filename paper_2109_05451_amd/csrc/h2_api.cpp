@@ -334,11 +334,10 @@ void each_launch(Plan& p, F f) {
   f(p.outc);
 }
 
-// Operators smaller than this are loaded without a look at the free memory.
-constexpr int64_t kCheckMemory = int64_t{1} << 30;
-
-// Build plans and upload; the handle's device is current.
-int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* d_dense) {
+// Build plans and upload; the handle's device is current.  group: the sweeps in
+// composed stages where the memory allows, else level by level; *grouped: they are.
+int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* d_dense, bool group, bool* grouped) {
+  *grouped = false;
   const int64_t q = P.q, n = P.n;
   const int64_t* lp = P.level_ptr;
   h->n = n; h->q = q; h->nnodes = P.nnodes; h->nleaves = P.nleaves; h->leaf0 = P.leaf0;
@@ -451,19 +450,24 @@ int build_handle(const uint8_t* buf, const Parsed& P, h2_op_s* h, const double* 
     RowBases B;
     B.ld_x = n;
     B.ld_h = H;
-    compose_sweeps(lay, B, false, ntrans, true, &cn);
+    compose_sweeps(lay, B, false, ntrans, group, &cn);
     if (!composed_fits(cn)) compose_sweeps(lay, B, false, ntrans, false, &cn);
     if (!h->shared) {
-      compose_sweeps(lay, B, true, cn.ntrans, true, &ct);
+      compose_sweeps(lay, B, true, cn.ntrans, group, &ct);
       if (!composed_fits(ct)) compose_sweeps(lay, B, true, cn.ntrans, false, &ct);
     }
-    // composed rows are extra memory (a few per cent of a large operator): not
-    // taken where the operator then no longer fits
+    // Composed rows are extra memory: 17 to 31% of the stored data at 4096 to
+    // 56 000 points (2D, rank 16 and 36), 14% at 100 003, 5% from 2^18 on.  They
+    // are not taken where a workspace of 64 columns and a copy of the matrix
+    // data (h2_tune, FP32) would then no longer fit beside the operator.
     const int64_t need = P.off_end - P.off_U + 8 * (h->shared ? cn : ct).ntrans;
     size_t free_b = 0, total_b = 0;
-    if (need > kCheckMemory && hipMemGetInfo(&free_b, &total_b) == hipSuccess && need + need / 16 > (int64_t)free_b) {
+    *grouped = !cn.stages.empty() || !ct.stages.empty();
+    if (*grouped && hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
+        2 * need + ws_bytes(n, H, kPassVectorsMfma) > (int64_t)free_b) {
       compose_sweeps(lay, B, false, ntrans, false, &cn);
       if (!h->shared) compose_sweeps(lay, B, true, cn.ntrans, false, &ct);
+      *grouped = false;
     }
     int rc;
     if ((rc = add_composed(h, cn, h->planN)) != H2_OK) return rc;
@@ -733,16 +737,26 @@ int load_common(const uint8_t* buf, int64_t len, int device, h2_handle* out, con
   if (!guard.ok) { set_error("hipSetDevice failed"); return H2_EHIP; }
   int ncu = 0;
   HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device), "hipDeviceGetAttribute");
-  h2_op_s* h = new (std::nothrow) h2_op_s();
-  if (!h) { set_error("out of host memory"); return H2_ENOMEM; }
-  h->device = device;
-  h->dense_stream_grid = 2 * (int64_t)std::max(ncu, 1);
-  try {
-    rc = build_handle(buf, P, h, d_dense);
-    h->file_len = len;
-  } catch (const std::bad_alloc&) {
-    set_error("out of host memory while building schedules");
-    rc = H2_ENOMEM;
+  h2_op_s* h = nullptr;
+  for (bool group = true;;) {
+    h = new (std::nothrow) h2_op_s();
+    if (!h) { set_error("out of host memory"); return H2_ENOMEM; }
+    h->device = device;
+    h->dense_stream_grid = 2 * (int64_t)std::max(ncu, 1);
+    bool grouped = false;
+    try {
+      rc = build_handle(buf, P, h, d_dense, group, &grouped);
+      h->file_len = len;
+    } catch (const std::bad_alloc&) {
+      set_error("out of host memory while building schedules");
+      rc = H2_ENOMEM;
+    }
+    // an allocation that fails although the memory is there (or was): without the composed rows
+    if (rc != H2_ENOMEM || !grouped) break;
+    (void)hipGetLastError();
+    free_device(h);
+    delete h;
+    group = false;
   }
   // the no-allocation product's stream and events, and the device address
   // of its scratch array on this device

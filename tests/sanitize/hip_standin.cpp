@@ -72,7 +72,7 @@ std::set<GraphExec*> g_execs;
 std::vector<OpP> g_pending;
 std::map<void*, size_t> g_mem;
 size_t g_used = 0, g_peak = 0, g_limit = size_t(1) << 34;
-bool g_hide_free = false;
+int g_hide_free = 0;
 uint64_t g_seed = 1;
 std::map<std::string, int64_t> g_count;
 Stream g_null;
@@ -176,7 +176,8 @@ void h2_standin_limit(int64_t free_bytes) {  // free device memory from now on (
   Lock l(g_mu);
   g_limit = free_bytes < 0 ? size_t(1) << 34 : g_used + (size_t)free_bytes;
 }
-void h2_standin_hide_free(int hide) { Lock l(g_mu); g_hide_free = hide != 0; }  // hipMemGetInfo says that nothing is free
+// hipMemGetInfo tells the truth (0), that nothing is free (1), that all of it is (2)
+void h2_standin_hide_free(int hide) { Lock l(g_mu); g_hide_free = hide; }
 int64_t h2_standin_peak() {  // largest memory held beyond the present since the last call
   Lock l(g_mu);
   const int64_t p = (int64_t)g_peak - (int64_t)g_used;
@@ -197,7 +198,7 @@ hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipMemGetInfo(size_t* f, size_t* t) {
   Lock l(g_mu);
-  *f = g_hide_free ? 0 : g_limit - g_used;
+  *f = g_hide_free == 1 ? 0 : g_hide_free == 2 ? g_limit : g_limit - g_used;
   *t = g_limit;
   return hipSuccess;
 }

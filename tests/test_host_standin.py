@@ -93,3 +93,8 @@ def test_batch_tuned_while_a_replay_is_queued(exe, tmp_path):
 
 def test_fp32_input_copy_only_where_read(exe, tmp_path):
     run(exe, tmp_path, "fp32", reps()[:-1])
+
+
+def test_load_where_memory_is_short(exe, tmp_path):
+    run(exe, tmp_path, "memory", [h2gen.random_rep(5, q=5, max_children=2, max_leaf=6, max_rank=5, p_adm=0.3,
+                                                   separate=s, integer=False) for s in (False, True)])
