@@ -58,17 +58,18 @@ class Arena {
   // Room for `bytes` of later allocations in one device allocation (each one
   // and its release cost tens of microseconds); where it would take over half of
   // the free memory, they are made one by one.
-  void reserve(size_t bytes) {
+  bool reserve(size_t bytes) {
     void* p = nullptr;
     size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || bytes > free_b / 2) return;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || bytes > free_b / 2) return false;
     if (hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
-      return;
+      return false;
     }
     ptrs_.push_back(p);
     pool_ = static_cast<uint8_t*>(p);
     pool_left_ = bytes;
+    return true;
   }
   template <class T>
   int alloc(T** out, int64_t count, hipStream_t s) {
@@ -672,7 +673,10 @@ Sizes sizes_of(const Parsed& P, const std::vector<int64_t>& kr, const std::vecto
   return z;
 }
 
-int compress_impl(h2_op_s* h, double tau, hipStream_t s, h2_handle* out, h2_compress_info_t* info) {
+// reserve: the scratch in one allocation where that is at most half of the
+// free memory; *reserved: it was
+int compress_impl(h2_op_s* h, double tau, hipStream_t s, h2_handle* out, h2_compress_info_t* info, bool reserve,
+                  bool* reserved) {
   hipEvent_t ev[6] = {};
   for (auto& e : ev) CK(hipEventCreate(&e), "hipEventCreate");
   struct EvGuard {
@@ -752,7 +756,7 @@ int compress_impl(h2_op_s* h, double tau, hipStream_t s, h2_handle* out, h2_comp
     int64_t all = per * (sep ? 2 : 1) + 4 * old.U + 3 * old.E + (sep ? 4 * old.V + 3 * old.F : 0);
     all += all / 8 + (int64_t)(48 << 20) / 8;
     if (old.S <= all) all += 2 * old.S;
-    C.ar.reserve(sizeof(double) * (size_t)all);
+    if (reserve) *reserved = C.ar.reserve(sizeof(double) * (size_t)all);
   }
   RC(C.ar.alloc(&C.So, old.S, s));
   Tree Xr, Xc;
@@ -922,7 +926,13 @@ int h2_compress(h2_handle h, double tau, h2_handle* out, h2_compress_info_t* inf
   }
   int rc;
   try {
-    rc = compress_impl(h, tau, static_cast<hipStream_t>(stream), out, info);
+    bool reserved = false;
+    rc = compress_impl(h, tau, static_cast<hipStream_t>(stream), out, info, true, &reserved);
+    // the reservation may be what left too little for the new operator
+    if (rc == H2_ENOMEM && reserved) {
+      (void)hipGetLastError();
+      rc = compress_impl(h, tau, static_cast<hipStream_t>(stream), out, info, false, &reserved);
+    }
   } catch (const std::bad_alloc&) {
     set_error("out of host memory in recompression");
     rc = H2_ENOMEM;

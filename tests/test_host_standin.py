@@ -98,3 +98,9 @@ def test_fp32_input_copy_only_where_read(exe, tmp_path):
 def test_load_where_memory_is_short(exe, tmp_path):
     run(exe, tmp_path, "memory", [h2gen.random_rep(5, q=5, max_children=2, max_leaf=6, max_rank=5, p_adm=0.3,
                                                    separate=s, integer=False) for s in (False, True)])
+
+
+def test_recompression_where_memory_is_short(exe, tmp_path):
+    # mostly dense blocks: the new handle is larger than the scratch
+    run(exe, tmp_path, "compress_memory", [h2gen.random_rep(3, q=1, max_children=40, max_leaf=255, max_rank=2,
+                                                            p_adm=0.02, integer=False, allow_empty=False)])
