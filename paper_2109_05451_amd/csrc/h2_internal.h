@@ -321,7 +321,7 @@ struct Composed {
 // the operator's transposed array from element `first` on.
 // group: false keeps one level per stage.
 void compose_sweeps(const OpLayout& L, const RowBases& B, bool trans_op, int64_t first, bool group, Composed* C);
-// True when every row fits the tabled kernels.
+// True when every row fits the tabled kernels, and every stage of several levels one launch.
 bool composed_fits(const Composed& C);
 void append_row(RowTables& t, const RowSpec& r);
 int64_t row_cols(const RowSpec& r);

@@ -327,11 +327,16 @@ void compose_sweeps(const OpLayout& L, const RowBases& B, bool trans_op, int64_t
 }
 
 bool composed_fits(const Composed& C) {
+  // up to four workgroups of 256 threads a row (64 vectors), 2^32 - 1 threads a launch
+  constexpr size_t kMaxSplitRows = (size_t(1) << 22) - 1;
   for (const auto* v : {&C.up, &C.down})
-    for (const auto& rows : *v)
-      for (const RowSpec& r : rows)
+    for (size_t i = 0; i < v->size(); ++i) {
+      const bool split = (v == &C.up ? C.up_split : C.down_split)[i] != 0;
+      if (split && (*v)[i].size() > kMaxSplitRows) return false;
+      for (const RowSpec& r : (*v)[i])
         if ((int64_t)r.blks.size() > kNbMax) return false;
-  return true;
+    }
+  return !C.out_split || C.out.size() <= kMaxSplitRows;
 }
 
 void append_row(RowTables& t, const RowSpec& r) {

@@ -14,7 +14,7 @@
 #include <string>
 #include <vector>
 
-#include "h2.h"
+#include "h2_internal.h"
 
 extern "C" {
 void h2_standin_seed(uint64_t);
@@ -329,6 +329,22 @@ void fp32(const std::vector<File>& files, hipStream_t s) {
   if (!split) fail("schedule 3 taken as 2 everywhere");
 }
 
+// Stages of several levels with more rows than one launch of four workgroups a
+// row can hold are taken level by level.
+void split_rows(const std::vector<File>&, hipStream_t) {
+  for (bool split : {false, true})
+    for (size_t rows : {size_t(1) << 20, (size_t(1) << 22) - 1, size_t(1) << 22})
+      for (int where = 0; where < 3; ++where) {
+        h2::Composed c;
+        std::vector<h2::RowSpec> v(rows);
+        if (where == 0) c.up.push_back(std::move(v)), c.up_split.push_back(split);
+        if (where == 1) c.down.push_back(std::move(v)), c.down_split.push_back(split);
+        if (where == 2) c.out = std::move(v), c.out_split = split;
+        const bool fits = !split || 4 * rows * 256 < size_t(1) << 32;
+        if (h2::composed_fits(c) != fits) fail(name_of("rows", (int64_t)rows, split, where, ' '));
+      }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -347,6 +363,7 @@ int main(int argc, char** argv) {
   else if (name == "memory") memory(files, s);
   else if (name == "compress_memory") compress_memory(files, s);
   else if (name == "fp32") fp32(files, s);
+  else if (name == "split_rows") split_rows(files, s);
   else return 2;
   if (h2_standin_live() != live) fail("streams, events, graphs or memory left behind");
   (void)hipStreamDestroy(s);

@@ -104,3 +104,7 @@ def test_recompression_where_memory_is_short(exe, tmp_path):
     # mostly dense blocks: the new handle is larger than the scratch
     run(exe, tmp_path, "compress_memory", [h2gen.random_rep(3, q=1, max_children=40, max_leaf=255, max_rank=2,
                                                             p_adm=0.02, integer=False, allow_empty=False)])
+
+
+def test_composed_stages_fit_a_launch(exe, tmp_path):
+    run(exe, tmp_path, "split_rows", reps(range(1)))
