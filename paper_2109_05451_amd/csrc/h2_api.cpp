@@ -124,7 +124,6 @@ void add_stream_rows(h2_op_s* h, const std::vector<RowSpec>& rows, const size_t*
       append_row(h->rt, r);
       narrow.max_rows = std::max(narrow.max_rows, r.nrows);
       if (r.nrows > 0) narrow.min_rows = std::min(narrow.min_rows, r.nrows);
-      narrow.max_cols = std::max(narrow.max_cols, row_cols(r));
     } else {
       append_row(h->wide, r);
       wide.max_rows = std::max(wide.max_rows, r.nrows);
@@ -835,13 +834,7 @@ int run_launch(h2_op_s* h, const Workspace& w, const Launch& L, int nv, const Ep
   }(lowp ? H2_PREC_FP32 : H2_PREC_FP64);
   int kcw = L.kcp[lowp ? H2_PREC_FP32 : H2_PREC_FP64], occ = L.occp[lowp ? H2_PREC_FP32 : H2_PREC_FP64];
   if (nvp > 0 && kcw == kAutoForm) {
-    RowForm f = auto_form(nvp, L.row_count, L.max_rows);
-    // dense rows beside the BF16 sweeps, one vector tile, rows of up to 1536
-    // columns (2D): there the sweeps' chain is what the product waits for, and
-    // the LDS-staged kernel leaves it more of the memory (20 000 points 188
-    // against 204-219 us, 82 810 points 245 against 270; longer rows, 3D of
-    // 32 768 points, 784 against 649)
-    if (!L.lowrank && prec == H2_PREC_BF16 && nvp == 16 && L.max_cols <= 1536) f = {64, 0};
+    const RowForm f = auto_form(nvp, L.row_count, L.max_rows);
     kcw = f.kc;
     occ = f.occ;
   }
@@ -1163,7 +1156,6 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
       L.row_count += dense2[0].row_count;
       L.max_rows = std::max(L.max_rows, dense2[0].max_rows);
       L.min_rows = std::min(L.min_rows, dense2[0].min_rows);
-      L.max_cols = std::max(L.max_cols, dense2[0].max_cols);
       L.slots = L.slots && dense2[0].slots ? std::max(L.slots, dense2[0].slots) : 0;
       STEP(run_launch(h, w, L, nv, ep, side, nvp, -1, prec));
     } else

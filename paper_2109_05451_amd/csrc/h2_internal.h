@@ -114,7 +114,6 @@ struct Launch {
   int mode = MODE_STORE;
   int64_t row_begin = 0, row_count = 0;  // slice of the kind's row table
   int32_t max_rows = 0;                   // largest output length of its rows
-  int64_t max_cols = 0;                   // most input columns of its rows
   int slots = 0;                          // transposed rows: form of the streaming kernel (cols_slots)
   int32_t min_rows = kMaxDim;             // smallest output length of its rows that is not zero
   bool split = false;                     // composed sweep rows of several levels (launch_split_rows on the MFMA path)
@@ -324,7 +323,6 @@ void compose_sweeps(const OpLayout& L, const RowBases& B, bool trans_op, int64_t
 // True when every row fits the tabled kernels, and every stage of several levels one launch.
 bool composed_fits(const Composed& C);
 void append_row(RowTables& t, const RowSpec& r);
-int64_t row_cols(const RowSpec& r);
 int64_t row_work(const RowSpec& r);
 // Places the fragment-ordered copy of rows [begin, end) of t: rows with the
 // same matrix (array, offset and shape) share one region; regions start at

@@ -373,12 +373,10 @@ void place_fl(RowTables& t, int64_t begin, int64_t end, int arr, FlKeys* keys, i
   }
 }
 
-int64_t row_cols(const RowSpec& r) {
+int64_t row_work(const RowSpec& r) {
   int64_t c = 0;
   for (const BlockRef& b : r.blks) c += b.width;
-  return c;
+  return c * r.nrows;
 }
-
-int64_t row_work(const RowSpec& r) { return row_cols(r) * r.nrows; }
 
 }  // namespace h2
