@@ -99,7 +99,11 @@ typedef struct {
 
 /* Per-phase GPU time accumulated over the h2_gemv calls made while profiling
  * was on (h2_profile), measured with HIP events recorded on the stream each
- * phase runs on.  Times in milliseconds. */
+ * phase runs on.  Times in milliseconds.  Where a small operator's FP64
+ * product of op 'N' with up to 4 vectors runs in three launches (an "input"
+ * line in h2_plan_info), the first one -- input permutation, dense rows and
+ * upsweep together -- counts as the upsweep, and the permutation, downsweep
+ * and dense times are those of two events in a row. */
 typedef struct {
   int64_t calls;          /* h2_gemv calls profiled */
   double ms_permute;      /* input permutation into tree order */

@@ -1107,14 +1107,19 @@ int gemv_pass(h2_op_s* h, const Workspace& w, bool trans, double alpha, const do
   int rc;
 #define STEP(x) do { if ((rc = (x)) != H2_OK) return rc; } while (0)
   // small operators on the streaming path: three launches in a row, no side
-  // stream (the general sequence when its phases are to be timed)
-  if (nvp == 0 && comp && !trans && !ev && plan.first.row_count > 0) {
+  // stream (profiled: the first launch is the upsweep phase, the phases that
+  // it or nothing else runs have empty intervals)
+  if (nvp == 0 && comp && !trans && plan.first.row_count > 0) {
+    for (int i : {0, 5, 9, 10, 6, 11, 12, 1}) STEP(mark(i, s));
     const FirstArgs F{h->d_perm, ldx, plan.first_dense, h->d_trans, w.xh};
     HIP_TRY(launch_rows_first(h->rt.d_rows + plan.first.row_begin, plan.first.row_count, h->rt.d_colend,
                               h->rt.d_in_off, h->d_mat, X, w.zn, nv, F, s),
             "kernel launch");
+    STEP(mark(2, s));
     for (const Launch& L : plan.couple) STEP(run_launch(h, w, L, nv, ep, s));
-    return run_launch(h, w, plan.outc, nv, ep, s);
+    for (int i : {3, 4, 7}) STEP(mark(i, s));
+    STEP(run_launch(h, w, plan.outc, nv, ep, s));
+    return mark(8, s);
   }
   STEP(mark(0, s));
   if (nvp) HIP_TRY(launch_permute_in_rm(X, ldx, h->d_pinv, w.xt, h->n, nv, nvp, s), "permute");

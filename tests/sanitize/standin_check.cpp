@@ -329,6 +329,32 @@ void fp32(const std::vector<File>& files, hipStream_t s) {
   if (!split) fail("schedule 3 taken as 2 everywhere");
 }
 
+// Profiled products run the launches that unprofiled ones run.
+void profile(const std::vector<File>& files, hipStream_t s) {
+  const char* names[] = {"rows_first", "rows", "cols", "wave_rows", "split_rows", "split_dense", "wave_cols", "permute_in"};
+  bool first = false;
+  for (const File& f : files) {
+    Pair p(f);
+    first = first || plan_has(p.h, "input ");
+    for (char op : {'N', 'T'})
+      for (int64_t nv : {1, 4, 20}) {
+        std::vector<int64_t> n[2];
+        for (int on : {0, 1}) {
+          OK(h2_profile(p.h, on));
+          for (const char* k : names) n[on].push_back(-h2_standin_count(k));
+          product(p, op, nv, 0, s, "profiled");
+          for (size_t k = 0; k < n[on].size(); ++k) n[on][k] += h2_standin_count(names[k]);
+        }
+        if (n[0] != n[1]) fail(name_of("profiled launches", nv, 0, 0, op));
+        h2_profile_t t;
+        OK(h2_profile_read(p.h, &t));
+        if (t.calls != 1) fail("profiled calls");
+      }
+    OK(h2_profile(p.h, 0));
+  }
+  if (!first) fail("no operator of three launches");
+}
+
 // Stages of several levels with more rows than one launch of four workgroups a
 // row can hold are taken level by level.
 void split_rows(const std::vector<File>&, hipStream_t) {
@@ -363,6 +389,7 @@ int main(int argc, char** argv) {
   else if (name == "memory") memory(files, s);
   else if (name == "compress_memory") compress_memory(files, s);
   else if (name == "fp32") fp32(files, s);
+  else if (name == "profile") profile(files, s);
   else if (name == "split_rows") split_rows(files, s);
   else return 2;
   if (h2_standin_live() != live) fail("streams, events, graphs or memory left behind");

@@ -108,3 +108,7 @@ def test_recompression_where_memory_is_short(exe, tmp_path):
 
 def test_composed_stages_fit_a_launch(exe, tmp_path):
     run(exe, tmp_path, "split_rows", reps(range(1)))
+
+
+def test_profiled_products_run_the_same_launches(exe, tmp_path):
+    run(exe, tmp_path, "profile", reps())
