@@ -554,12 +554,12 @@ hipError_t launch_split_rows(const RowDesc* rows, int64_t nrows, const int32_t* 
                              int max_rows, hipStream_t s, bool all = false, int64_t grid = 0, int remap = 0);
 // True when launch_wave_rows has a second form (occ != 0) for this pass width
 inline bool wave_alt(int nvp, bool narrow) { return nvp != 48 && !narrow; }
-// dst[R.fl_off ...] = the fragment-ordered copy of every row's matrix at src[R.data_off ...]
 // The transposed rows of op 'T' on the multi-vector path (FP64, at most 64
 // outputs per row, any number of blocks): row-major out = sum of M_b^T x_b
 hipError_t launch_wave_cols(const RowDesc* rows, int64_t nrows, const int64_t* bdata, const int32_t* bmr,
                             const int64_t* bin, const double* data, const double* in, double* out, int nvp,
                             int max_rows, hipStream_t s);
+// dst[R.fl_off ...] = the fragment-ordered copy of every row's matrix at src[R.data_off ...]
 template <typename T>
 hipError_t launch_rows_to_fl(const RowDesc* rows, int64_t nrows, const int32_t* colend, const T* src, T* dst,
                              hipStream_t s);

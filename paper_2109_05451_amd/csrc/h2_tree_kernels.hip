@@ -1,4 +1,4 @@
-// Subtree-fused sweeps of the multi-vector path (FP64 and FP32 MFMA).
+// Subtree-fused sweeps of the multi-vector path (FP32 MFMA; FP64 runs composed stages instead).
 //
 // The upsweep (Algorithm 1: leaf products x^_t = V_t^T x_t, then the transfer
 // levels x^_p = sum_c F_c^T x^_c) and the downsweep (Algorithm 6: y^_c +=
@@ -26,17 +26,8 @@ namespace h2 {
 namespace {
 
 constexpr int kT = 256;
-typedef double d4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 template <typename T> struct Mfma;
-template <> struct Mfma<double> {
-  typedef d4 acc;
-  static __device__ __forceinline__ d4 op(double a, double b, d4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  // accumulator element r of lane l: row 4r + l/16, column l%16
-  static __device__ __forceinline__ int row(int r, int akk) { return 4 * r + akk; }
-};
 template <> struct Mfma<float> {
   typedef f4 acc;
   static __device__ __forceinline__ f4 op(float a, float b, f4 c) {
