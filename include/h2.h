@@ -194,10 +194,11 @@ int h2_gemv_noalloc(h2_handle h, char op, double alpha, const double* X, int64_t
  * afresh at every replay).  Up to 8 graphs are kept per handle, the least
  * recently used dropped first; retuning (h2_tune, h2_tune_set, h2_set_schedule,
  * h2_set_sweeps, h2_set_dense_grid, h2_set_fragment_order) and a call whose
- * workspace has to grow drop them all.  For repeated products on
- * the same buffers, where launching the sequence costs more than the GPU
- * work (small operators).  Calls on the null stream, or while profiling, are
- * not captured.  No memset nodes are captured.  Disabling drops the graphs.
+ * workspace has to grow drop them all.  For repeated products on the same
+ * buffers where launching the sequence costs more than the GPU work; a
+ * sequence of three launches (see h2_set_schedule) is faster launched (35
+ * against 41 us for 4096 points, one vector).  Calls on the null stream, or
+ * while profiling, are not captured.  No memset nodes are captured.  Disabling drops the graphs.
  * Synchronizes the device.  Errors: H2_EINVAL, H2_EHIP. */
 int h2_graph(h2_handle h, int enable);
 
@@ -325,7 +326,10 @@ int h2_set_dense_grid(h2_handle h, int64_t workgroups);
  *      beside the upper upsweep, the other levels' coupling rows and the
  *      upper downsweep; the last downsweep level waits for them (not with
  *      the fused sweeps, nor for FP32 passes of 64 vectors whose coupling rows
- *      run the LDS-staged kernel, which take schedule 2 instead)
+ *      run the LDS-staged kernel, nor where the FP64 downsweep is one composed
+ *      stage, small operators, which take schedule 2 instead)
+ * Op 'T', and a small operator's product of up to 4 vectors in three launches
+ * (an "input" line in h2_plan_info), have no schedule.
  * Until set or tuned: 2 on operators of fewer than 8192 leaves (multi-vector)
  * or 2048 (streaming), else 0.  Results are bitwise the same; h2_tune keeps the
  * fastest.  Synchronizes the device.  Errors: H2_EINVAL. */

@@ -842,7 +842,7 @@ __global__ __launch_bounds__(kT) void k_rows_t(const RowDesc* __restrict__ rows,
 // a fixed order.  R.pad holds the row's largest block height.
 // Bound by HBM; the kernel it takes over from copied each block through LDS
 // with a barrier and an integer division per element.  2D, 2^18 points, one
-// vector: coupling rows 731 -> 209 us (6.4 TB/s of blocks), product 1.34 -> 0.54 ms.
+// vector: coupling rows 731 -> 204 us (6.6 TB/s counted), product 1.39 -> 0.63 ms.
 template <int NVB, int SL>
 __global__ __launch_bounds__(kT) void k_cols(const RowDesc* __restrict__ rows, int64_t nrows,
                                              const int64_t* __restrict__ bdata, const int32_t* __restrict__ bmr,

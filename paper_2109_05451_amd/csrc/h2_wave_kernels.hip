@@ -57,7 +57,8 @@ constexpr int kChunk = 1024;  // columns of one source-row table (4 KB of LDS pe
 // Measured on the 2D operator of 2^20 points (rank 36, 517 772 coupling
 // blocks), against the best kernel before: coupling launch 1.13 -> 1.08 ms at
 // 16 vectors, 2.62 -> 1.83 ms (47 TF) at 64; half of the dense rows 1.19 ->
-// 0.87 ms (52 TF) at 64; whole products 2.96 -> 2.85 and 6.94 -> 5.36 ms.
+// 0.87 ms (52 TF) at 64; whole products 2.96 -> 2.85 and 6.94 -> 5.36 ms (2.80
+// and 5.12 with the composed sweeps and the later output permutation).
 // Lanes of rows past m and of columns past ncols read whatever follows (the
 // arrays end in kRowSlack bytes of slack): the former's outputs are not
 // stored, the latter's operands are zeroed.
@@ -409,7 +410,9 @@ __global__ __launch_bounds__(kT, W) void k_wave_rows(const RowDesc* __restrict__
 // Bound by the bytes, as the streaming of the same blocks untransposed: one
 // pass over the matrix for up to 64 vectors, where passes of four vectors
 // through LDS read it once per four.  Measured on the 2D operator of 100 003
-// points (leaf 50, rank 25) at 24 vectors: product 3.80 -> 0.60 ms.
+// points (leaf 50, rank 25) at 24 vectors: product 3.80 -> 0.53-0.57 ms.  At 32
+// to 64 vectors a group is eight rows, 64 bytes of a column: half of each line
+// is fetched again (3.5 GB counted for 0.85).
 // KS: a workgroup per row and vector range, its blocks dealt to the four waves
 // in turn and their partial sums added through LDS in wave order: for launches
 // of too few rows to give every SIMD four waves, where a row's chain of loads
